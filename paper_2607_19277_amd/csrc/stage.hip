@@ -210,11 +210,11 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
         to_prim_z<RS>(C1, gamma, gm1, wk1, ok);
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const R sm = slope<LIM>(wm1[v] - wm2[v], wk[v] - wm1[v]);
-            wL[v] = wm1[v] + R(0.5) * sm;
-            const R s0 = slope<LIM>(wk[v] - wm1[v], wk1[v] - wk[v]);
-            wR[v] = wk[v] - R(0.5) * s0;
-            wLz[v] = wk[v] + R(0.5) * s0;
+            const R sm = half_slope<LIM>(wm1[v] - wm2[v], wk[v] - wm1[v]);
+            wL[v] = wm1[v] + R(HALF<LIM>) * sm;
+            const R s0 = half_slope<LIM>(wk[v] - wm1[v], wk1[v] - wk[v]);
+            wR[v] = wk[v] - R(HALF<LIM>) * s0;
+            wLz[v] = wk[v] + R(HALF<LIM>) * s0;
         }
         riemann<RS, R>(wL, wR, gammaR, igm1R, Flo);
         put_plane(k0 & 1, wk, G0, 0);
@@ -252,9 +252,9 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
             to_prim_z<RS>(C2, gamma, gm1, wk2, ok);
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                const R s1 = slope<LIM>(wk1[v] - wk[v], wk2[v] - wk1[v]);
-                wR[v] = wk1[v] - R(0.5) * s1;
-                wLn[v] = wk1[v] + R(0.5) * s1;
+                const R s1 = half_slope<LIM>(wk1[v] - wk[v], wk2[v] - wk1[v]);
+                wR[v] = wk1[v] - R(HALF<LIM>) * s1;
+                wLn[v] = wk1[v] + R(HALF<LIM>) * s1;
             }
             riemann<RS, R>(wLz, wR, gammaR, igm1R, Fhi);
             put_plane(nxt, wk1, Gn, RS != 3 ? 0 : 1 + cur);
@@ -293,9 +293,10 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
             R wL[NV], wR[NV], F[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                const R d0 = c[1][v] - c[0][v], d1 = c[2][v] - c[1][v], d2 = c[3][v] - c[2][v];
-                wL[v] = c[1][v] + R(0.5) * slope<LIM>(d0, d1);
-                wR[v] = c[2][v] - R(0.5) * slope<LIM>(d1, d2);
+                R s0, s1;
+                half_slopes<LIM>(c[1][v] - c[0][v], c[2][v] - c[1][v], c[3][v] - c[2][v], s0, s1);
+                wL[v] = c[1][v] + R(HALF<LIM>) * s0;
+                wR[v] = c[2][v] - R(HALF<LIM>) * s1;
             }
             riemann<RS, R>(wL, wR, gammaR, igm1R, F);
             sF[cur][0][t] = F[0];

@@ -1,0 +1,56 @@
+"""Every regime of the Riemann fluxes on an MI355X against the CPU oracle:
+supersonic flow along each axis in both directions, mixed sub- and supersonic
+faces with both signs of the contact speed, and gas at rest; each solver with
+both limiters, on a mesh with a level jump.  One step from the same state to
+the FP64 bar of the repository (1e-12)."""
+from __future__ import annotations
+
+import pytest
+
+from oracle.oracle import Oracle
+from paper_2607_19277_amd import workloads as W
+from parity import TOL_FP64, parity_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def agile():
+    import torch
+    assert torch.cuda.is_available(), "needs a GPU"
+    from paper_2607_19277_amd import agile as A
+    A.lib()
+    return A
+
+
+# bulk velocity, factor of the smooth state's own velocities (below 0.3)
+FLOWS = {"+x": ((4.0, 0, 0), 1.0), "-y": ((0, -4.0, 0), 1.0), "+z": ((0, 0, 4.0), 1.0),
+         "mixed": ((0, 0, 0), 12.0), "rest": ((0, 0, 0), 0.0)}
+SOLVERS = {"hll": W.HLL, "hllc": W.HLLC, "lf": W.LF}
+
+
+def _workload(flow, riemann, limiter):
+    w = W.smooth_random(W.refine_blocks(W.uniform_blocks((2, 2, 2)), [3]), (2, 2, 2), 2, seed=6)
+    rho = w.U[:, 0]
+    u = w.U[:, 1:4] / rho[:, None]
+    p = (w.gamma - 1.0) * (w.U[:, 4] - 0.5 * rho * (u * u).sum(axis=1))
+    v = [bulk + FLOWS[flow][1] * u[:, d] for d, bulk in enumerate(FLOWS[flow][0])]
+    w.U = W.prim_to_cons(w.gamma, rho, *v, p)
+    w.riemann, w.limiter = riemann, limiter
+    return w
+
+
+@pytest.mark.parametrize("limiter", [W.MINMOD, W.VANLEER])
+@pytest.mark.parametrize("solver", list(SOLVERS))
+@pytest.mark.parametrize("flow", list(FLOWS))
+def test_step_in_every_flux_regime(agile, flow, solver, limiter):
+    w = _workload(flow, SOLVERS[solver], limiter)
+    o = Oracle(w)
+    dt = o.dt()
+    m = agile.Mesh.from_workload(w)
+    assert m.dt() == dt
+    m.step(dt)
+    U = m.readback()
+    o.step(dt)
+    assert parity_error(U, o.state(), w.gamma).max() <= TOL_FP64
+    m.close()
