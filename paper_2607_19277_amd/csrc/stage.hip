@@ -6,17 +6,21 @@
 // 256 lanes = 4 wave64; lane (i, j) owns the z-column (i, j) of the block.
 // The block is marched plane by plane in z (2.5-D):
 //   - the conserved values of the column are streamed through a register
-//     ring (cells k, k+1, k+2) with the next cell (k+3) and the next plane's
-//     x/y ghosts prefetched one iteration ahead, so each interior value is
-//     read from HBM once per stage;
+//     ring (cells k, k+1 and k+2, the last one arriving while the plane's x
+//     and y faces are computed), so each interior value is read from HBM once
+//     per stage;
 //   - z faces: each lane keeps the primitives of cells k, k+1 and the left
 //     PLM state of face k+1/2, and computes one z-face flux per plane;
 //   - x/y faces of plane k: the plane's primitives (interior + 2 ghost
 //     columns / rows) go to LDS (double-buffered: plane k+1 is written while
-//     plane k's faces are computed, one barrier per plane) and 544 face tasks
-//     (272 x, 272 y) are spread over the lanes; each face flux is computed exactly once (the paper
-//     evaluates both faces of every cell) and in a frame rotated to the face
-//     normal, so x and y faces run one instruction stream;
+//     plane k's faces are computed, one barrier per plane); every lane takes
+//     the lower x and the lower y face of its own cell (its own state from
+//     registers, the three others from LDS at fixed offsets), and the 16 + 16
+//     upper faces of the plane are one wave's extra task; each face flux is
+//     computed exactly once (the paper evaluates both faces of every cell)
+//     and read back from LDS by the cell below it;
+//   - waves 0 and 1 (rotated over blocks) also load and convert the plane's
+//     128 ghost cells, waves 2 and 3 take the extra face task in turn;
 //   - update: L = -((dFx + dFy) + dFz)/dx, then
 //     SSP-RK2 stage 1: U1 = U + dt L;  stage 2: U' = (U^n + (U1 + dt L))/2;
 //     SSP-RK3: U1 = U + dt L, U2 = 3/4 U^n + 1/4 (U1 + dt L),
@@ -36,10 +40,13 @@ namespace agile {
 namespace {
 
 constexpr int NV = 5;
-constexpr int PW = BN + 2 * NG;      // 20: padded plane width
-constexpr int PLANE = PW * PW;       // 400
-constexpr int NXF = BN * (BN + 1);   // 272 x-face (and y-face) tasks per plane
-constexpr int NTASK = 2 * NXF;       // 544
+// A plane's primitives in LDS, per variable: the two lower y ghost rows (16
+// each), the 16 rows with their x ghosts (20 each), the two upper y ghost rows.
+constexpr int PW = BN + 2 * NG;
+constexpr int PMID = NG * BN, PTOP = PMID + BN * PW, PLANE = PTOP + NG * BN;   // 32, 352, 384
+// Its face fluxes: the lower y ones in lane order, the upper y ones, the 17 x
+// faces of every row.
+constexpr int FYTOP = BN * BN, FX = FYTOP + BN, NFX = BN + 1, NFACE = FX + BN * NFX;   // 256, 272, 17, 544
 
 // Workgroups are dealt to the 8 XCDs of the chip round-robin.  With xcd = 1
 // each XCD gets one contiguous range of work items (blocks in level + Morton
@@ -68,6 +75,18 @@ __device__ __forceinline__ void to_prim_z(const double C[NV], double gamma, doub
     w[0] = R(q[0]); w[1] = R(q[3]); w[2] = R(q[1]); w[3] = R(q[2]); w[4] = R(q[4]);
 }
 
+// A value at a wave-uniform base plus a lane offset in bytes: base in scalar
+// registers, so that the five variables of a cell cost one address
+// computation between them (the compiler would add the variable's stride to
+// 64-bit lane addresses).
+typedef __attribute__((address_space(1))) double gdouble;
+typedef __attribute__((address_space(1))) char gchar;
+__device__ __forceinline__ gdouble *uniform_at(const double *base, unsigned off) {
+    gchar *b = (gchar *)base;
+    asm("" : "+s"(b));
+    return (gdouble *)(b + off);
+}
+
 } // namespace
 
 #ifndef AGILE_STAGE_WAVES_F64
@@ -79,6 +98,15 @@ __device__ __forceinline__ void to_prim_z(const double C[NV], double gamma, doub
 
 // RS: 0 HLL, 1 HLLC, 2 local Lax-Friedrichs, 3 the SRHD module (local
 // Lax-Friedrichs on (rho, Gamma v, p)); LIM: 0 minmod, 1 van Leer;
+// Bound by VALU issue at 2 waves per SIMD (FP64; 3 with FP32 fluxes): the VALU
+// is busy for 53-65% of a launch, HBM for about half of its time.  Fixed face
+// ownership (no index arithmetic, no rotation selects, own state from
+// registers), ghosts converted once and wave-uniform addresses took an HLLC
+// first stage from 673 to 510 VALU instructions per wave and plane (1856
+// blocks: 263 -> 210 us).  Not faster: three waves per SIMD (168 registers;
+// the face work then spills or loses its instruction-level parallelism, 2-15%
+// slower), the upper faces of 8 planes at once from global memory (balanced
+// over the waves, 4% slower), cells loaded one plane further ahead (equal).
 // KIND: 1 first stage (U1 = U + dt L), 2 last SSP-RK2 stage
 // ((U^n + (U1 + dt L))/2), 3 middle SSP-RK3 stage (3/4 U^n + 1/4 (U1 + dt L)),
 // 4 last SSP-RK3 stage (1/3 U^n + 2/3 (U2 + dt L)).  The last stage of a step
@@ -86,10 +114,10 @@ __device__ __forceinline__ void to_prim_z(const double C[NV], double gamma, doub
 template <int RS, int LIM, int KIND, typename R>
 __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE_STAGE_WAVES_F32) void k_stage(StageArgs a) {
     constexpr bool FIRST = KIND == 1, LAST = KIND == 2 || KIND == 4;
-    // plane primitives and x/y face fluxes, double-buffered by plane parity so
+    // plane primitives and face fluxes, double-buffered by plane parity so
     // that one barrier per plane separates producers from consumers
     __shared__ R sP[2][NV][PLANE];
-    __shared__ R sF[2][NV][NTASK];
+    __shared__ R sF[2][NV][NFACE];
     __shared__ unsigned long long sMax[4];
 
     // work item = (block, slab of kslab planes)
@@ -107,102 +135,105 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
     const double gm1 = gamma - 1.0;
     const R gammaR = R(gamma), igm1R = R(1.0 / gm1);
     const double inv_dx = mp.inv_dx1 * double(1 << (D.level - 1));
-    const double dt = mp.dt;
+    const double dtdx = mp.dt * inv_dx;
     const size_t blk = size_t(b) * NV * CELLS;
     const double *Ub = a.Uin + blk;
     const int colp = j * 16 + i;
-    const int pown = (j + 2) * PW + i + 2;   // LDS position of this lane's own cell
+    const unsigned col8 = colp * 8;
     bool ok = true;
 
-    // conserved value source of this column's cell at z index kk in [-2, 18)
+    // conserved values of this column's cell at z index kk in [-2, 18)
     auto zload = [&](int kk, double C[NV]) {
-        const double *p;
-        int st;
-        if (kk >= 0 && kk < BN) {
-            p = Ub + kk * 256 + colp;
-            st = CELLS;
-        } else {
+        const double *p = Ub + kk * 256;
+        int st = CELLS;
+        if (kk < 0 || kk >= BN) {
             const int nb = kk < 0 ? D.nb[4] : D.nb[5];
             if (nb >= 0) {
-                p = a.Uin + size_t(nb) * NV * CELLS + (kk < 0 ? kk + BN : kk - BN) * 256 + colp;
-                st = CELLS;
+                p = a.Uin + size_t(nb) * NV * CELLS + (kk < 0 ? kk + BN : kk - BN) * 256;
             } else {
-                p = a.halo + size_t(-nb - 1) * NV * SLAB + (kk < 0 ? kk + NG : kk - BN) * 256 + colp;
+                p = a.halo + size_t(-nb - 1) * NV * SLAB + (kk < 0 ? kk + NG : kk - BN) * 256;
                 st = SLAB;
             }
         }
 #pragma unroll
-        for (int v = 0; v < NV; ++v) C[v] = p[v * st];
+        for (int v = 0; v < NV; ++v) C[v] = *uniform_at(p + v * st, col8);
     };
-    // x / y ghost cells of a plane: 32 per face, lanes 0..127; lanes 128..255
-    // repeat the same cells (same loads, same LDS slots and values), which
-    // keeps the plane loop free of branches
-    const int gf = (tid >> 5) & 3, gr = tid & 31;
-    int glp;   // LDS position of this lane's ghost cell
-    if (gf < 2) glp = ((gr >> 1) + 2) * PW + (gf == 0 ? (gr & 1) : BN + NG + (gr & 1));
-    else glp = (gf == 2 ? (gr >> 4) : BN + NG + (gr >> 4)) * PW + (gr & 15) + 2;
-    const int gnb = gf == 0 ? D.nb[0] : (gf == 1 ? D.nb[1] : (gf == 2 ? D.nb[2] : D.nb[3]));
-    auto gload = [&](int k, double G[NV]) {
-        const double *p;
-        int st;
-        if (gnb < 0) {
-            p = a.halo + size_t(-gnb - 1) * NV * SLAB + k * 32 + gr;
-            st = SLAB;
+    // roles of the waves, rotated over the work items: 0 and 1 convert the x
+    // and the y ghosts of a plane (64 each, one per lane), 2 and 3 take the
+    // extra face task of the even and of the odd planes
+    const int role = (__builtin_amdgcn_readfirstlane(tid >> 6) + item) & 3;
+    const int gf = 2 * (role & 1) + ((tid >> 5) & 1), gr = tid & 31;   // ghost face and cell
+    // its position in a plane's LDS copy, its source and the strides there
+    const int glp = gf == 0 ? PMID + (gr >> 1) * PW + (gr & 1)
+                            : (gf == 1 ? PMID + (gr >> 1) * PW + BN + NG + (gr & 1) : (gf == 2 ? gr : PTOP + gr));
+    const double *gsrc;
+    int gks, gst;
+    {
+        const int nb = gf == 0 ? D.nb[0] : (gf == 1 ? D.nb[1] : (gf == 2 ? D.nb[2] : D.nb[3]));
+        if (nb < 0) {
+            gsrc = a.halo + size_t(-nb - 1) * NV * SLAB + gr;
+            gks = 32;
+            gst = SLAB;
         } else if (gf < 2) {
-            p = a.XEin + (size_t(gnb) * NV * 2 + (gf == 0 ? 1 : 0)) * SLAB + k * 32 + gr;
-            st = 2 * SLAB;
+            gsrc = a.XEin + (size_t(nb) * NV * 2 + (gf == 0 ? 1 : 0)) * SLAB + gr;
+            gks = 32;
+            gst = 2 * SLAB;
         } else {
-            p = a.Uin + size_t(gnb) * NV * CELLS + k * 256 + (gf == 2 ? 224 : 0) + gr;
-            st = CELLS;
+            gsrc = a.Uin + size_t(nb) * NV * CELLS + (gf == 2 ? 224 : 0) + gr;
+            gks = 256;
+            gst = CELLS;
         }
+    }
+    auto gload = [&](int k, double G[NV]) {
+        const double *p = gsrc + size_t(k) * gks;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) G[v] = p[v * st];
+        for (int v = 0; v < NV; ++v) G[v] = p[v * gst];
     };
-    // SRHD ghosts: the con2prim is an iteration, and lanes 128.. would only
-    // repeat the ghost cells of lanes 0..127.  There, on even planes k lanes
-    // 0..127 convert the ghosts of plane k+1 and lanes 128.. those of plane
-    // k+2, which they keep (in G) and store on the odd plane k+1, when that
-    // LDS buffer is free; odd planes convert no ghost.  Each wave then does
-    // 1.5 con2prims per plane instead of 2.
-    const int gB = (RS == 3 && tid >= 128) ? 1 : 0;
-    // write a plane into LDS buffer `buf`: own cell (z-rotated primitives)
-    // and one ghost cell from its conserved values.  mode 0: every lane
-    // converts and stores its ghost; SRHD mode 1 (even plane): convert, lanes
-    // 128.. keep the result in G; mode 2 (odd plane): lanes 128.. store G.
-    auto put_plane = [&](int buf, const R w[NV], double G[NV], int mode) {
+    auto put_ghost = [&](int buf, const double G[NV]) {
+        double q[NV];
+        ok &= phys_prim<RS>(G, gamma, gm1, q);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) sP[buf][v][glp] = R(q[v]);
+    };
+    // LDS positions of this lane's own cell and of its y neighbours
+    const int pown = PMID + j * PW + NG + i;
+    auto yrow = [&](int r) { return r < 0 ? (r + NG) * BN + i : (r < BN ? PMID + r * PW + NG + i : PTOP + (r - BN) * BN + i); };
+    const int pym2 = yrow(j - 2), pym1 = yrow(j - 1), pyp1 = yrow(j + 1);
+    auto put_own = [&](int buf, const R w[NV]) {   // z-rotated primitives
         sP[buf][0][pown] = w[0]; sP[buf][1][pown] = w[2]; sP[buf][2][pown] = w[3];
         sP[buf][3][pown] = w[1]; sP[buf][4][pown] = w[4];
-        if (mode != 2) {
-            double q[NV];
-            ok &= phys_prim<RS>(G, gamma, gm1, q);
-            if (mode == 1 && gB) {
+    };
+    // flux from the four cells across a face
+    auto flux4 = [&](const R c0[NV], const R c1[NV], const R c2[NV], const R c3[NV], R F[NV]) __attribute__((always_inline)) {
+        R wL[NV], wR[NV];
 #pragma unroll
-                for (int v = 0; v < NV; ++v) G[v] = q[v];
-            } else {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) sP[buf][v][glp] = R(q[v]);
-            }
-        } else if (gB) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) sP[buf][v][glp] = R(G[v]);
+        for (int v = 0; v < NV; ++v) {
+            R s0, s1;
+            half_slopes<LIM>(c1[v] - c0[v], c2[v] - c1[v], c3[v] - c2[v], s0, s1);
+            wL[v] = c1[v] + R(HALF<LIM>) * s0;
+            wR[v] = c2[v] - R(HALF<LIM>) * s1;
         }
+        riemann<RS, R>(wL, wR, gammaR, igm1R, F);
+    };
+    // store a boundary face's flux (natural variable order) into register slot `slot`
+    auto keep = [&](int slot, int pos, R f0, R f1, R f2, R f3, R f4) {
+        double *r = a.freg + size_t(slot) * NV * REG + pos;
+        r[0] = double(f0); r[REG] = double(f1); r[2 * REG] = double(f2); r[3 * REG] = double(f3); r[4 * REG] = double(f4);
     };
 
-    // ---- prologue: cells k0-2 .. k0+2 of the column, face k0-1/2, plane k0 in
+    // ---- prologue: cells k0-2 .. k0+1 of the column, face k0-1/2, plane k0 in
     // LDS.  Its expressions are the loop body's; the library is built with
     // per-expression contraction only, so each expression rounds the same way
     // wherever it is compiled and results do not depend on the slab shape.
-    double C0[NV], C1[NV], C2[NV], Cn[NV], Gn[NV], Gn2[NV];
-    R wk[NV], wk1[NV], wLz[NV], Flo[NV], Fhi[NV];
+    double C0[NV], C1[NV];
+    R wk[NV], wk1[NV], wLz[NV], Flo[NV];
     {
         double Cm2[NV], Cm1[NV], G0[NV];
         zload(k0 - 2, Cm2);
         zload(k0 - 1, Cm1);
         zload(k0, C0);
         zload(k0 + 1, C1);
-        zload(k0 + 2, C2);
-        gload(k0, G0);
-        gload(min(k0 + 1 + gB, k1 - 1), Gn);
+        if (role < 2) gload(k0, G0);
         R wm2[NV], wm1[NV], wL[NV], wR[NV];
         to_prim_z<RS>(Cm2, gamma, gm1, wm2, ok);
         to_prim_z<RS>(Cm1, gamma, gm1, wm1, ok);
@@ -217,36 +248,88 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
             wLz[v] = wk[v] + R(HALF<LIM>) * s0;
         }
         riemann<RS, R>(wL, wR, gammaR, igm1R, Flo);
-        put_plane(k0 & 1, wk, G0, 0);
+        put_own(k0 & 1, wk);
+        if (role < 2) put_ghost(k0 & 1, G0);
     }
-    if (k0 == 0 && D.freg[4] >= 0) {
-        double *r = a.freg + size_t(D.freg[4]) * NV * REG + colp;
-        r[0] = double(Flo[0]); r[REG] = double(Flo[2]); r[2 * REG] = double(Flo[3]);
-        r[3 * REG] = double(Flo[1]); r[4 * REG] = double(Flo[4]);
-    }
+    if (k0 == 0 && D.freg[4] >= 0) keep(D.freg[4], colp, Flo[0], Flo[2], Flo[3], Flo[1], Flo[4]);
     __syncthreads();
 
-    const int tt = (tid + 64 * (item & 3)) & 255;   // rotate the extra x/y face tasks over the waves
     unsigned long long smax = 0;
     const int cf = D.cf_coarse;
     if (FIRST && slab == 0 && tid == 0) a.smax[b] = 0;   // the last stage takes the maximum
 
-    // One plane of the march.  The body has no branch before the barrier
-    // except the third face task: loads past the slab re-read its last valid
-    // cell or ghost row, and the last plane writes an unused LDS plane, so the
-    // z face, the plane store and the first two x/y tasks form one scheduling
-    // region.
+    // One plane of the march: plane k's x and y faces, z face k+1/2, plane
+    // k+1 into LDS (the last plane writes one that is not used), barrier,
+    // update of plane k.  The column's cell k+2 and the ghosts of plane k+1
+    // are loaded at the top and first used after the x and y faces.
     auto plane = [&](const int k) __attribute__((always_inline)) {
         const int cur = k & 1, nxt = cur ^ 1;
-        // SRHD: ghosts load on odd planes only (see put_plane)
-        const bool gl = RS != 3 || cur == 1;
-        // prefetch: z cell k+3, ghosts of plane k+2 (SRHD lanes 128..: k+3),
-        // U^n of plane k (stage 2)
-        zload(min(k + 3, k1 + NG - 1), Cn);
-        if (gl) gload(min(k + 2 + gB, k1 - 1), Gn2);
-        double Un[NV];
+        double C2[NV], G[NV], Un[NV];
+        zload(k + 2, C2);
+        if (role < 2) gload(min(k + 1, k1 - 1), G);
 
-        // (A) z face k+1/2, and plane k+1 into the other LDS buffer
+        // (A) lower x and y face of the own cell, and the plane's upper faces
+        R Fx[NV], Fy[NV];
+        {
+            R c0[NV], c1[NV], c3[NV];
+            const R c2[NV] = {wk[0], wk[2], wk[3], wk[1], wk[4]};
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                c0[v] = sP[cur][v][pown - 2];
+                c1[v] = sP[cur][v][pown - 1];
+                c3[v] = sP[cur][v][pown + 1];
+            }
+            flux4(c0, c1, c2, c3, Fx);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) sF[cur][v][FX + j * NFX + i] = Fx[v];
+        }
+        {
+            constexpr int nv[NV] = {0, 2, 1, 3, 4};   // rotated to the y normal: (rho, vy, vx, vz, p)
+            R c0[NV], c1[NV], c3[NV], F[NV];
+            const R c2[NV] = {wk[0], wk[3], wk[2], wk[1], wk[4]};
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                c0[v] = sP[cur][nv[v]][pym2];
+                c1[v] = sP[cur][nv[v]][pym1];
+                c3[v] = sP[cur][nv[v]][pyp1];
+            }
+            flux4(c0, c1, c2, c3, F);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                Fy[nv[v]] = F[v];
+                sF[cur][nv[v]][colp] = F[v];
+            }
+        }
+        if (role == 2 + cur) {
+            const int t = tid & 15;
+            const bool yd = tid & 16;
+            if (!(tid & 32)) {   // lanes 0..15: upper x face of row t; 16..31: upper y face of column t
+                const int p0 = yd ? PMID + (BN - 2) * PW + NG + t : PMID + t * PW + BN;
+                const int p1 = p0 + (yd ? PW : 1), p2 = yd ? PTOP + t : p0 + 2, p3 = yd ? PTOP + BN + t : p0 + 3;
+                const int v1 = yd ? 2 : 1, v2 = yd ? 1 : 2;
+                R c0[NV], c1[NV], c2[NV], c3[NV], F[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const R *q = sP[cur][v == 1 ? v1 : (v == 2 ? v2 : v)];
+                    c0[v] = q[p0]; c1[v] = q[p1]; c2[v] = q[p2]; c3[v] = q[p3];
+                }
+                flux4(c0, c1, c2, c3, F);
+                const int o = yd ? FYTOP + t : FX + t * NFX + BN;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) sF[cur][v == 1 ? v1 : (v == 2 ? v2 : v)][o] = F[v];
+                const int slot = yd ? D.freg[3] : D.freg[1];
+                if (slot >= 0) keep(slot, k * 16 + t, F[0], yd ? F[2] : F[1], yd ? F[1] : F[2], F[3], F[4]);
+            }
+        }
+
+        // U^n of plane k, for the update after the barrier
+        const unsigned cell8 = col8 + k * 2048;
+        if (!FIRST) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) Un[v] = __builtin_nontemporal_load(uniform_at(a.Un + blk + v * CELLS, cell8));
+        }
+        // (B) z face k+1/2, and plane k+1 into the other LDS buffer
+        R Fhi[NV];
         {
             R wk2[NV], wR[NV], wLn[NV];
             to_prim_z<RS>(C2, gamma, gm1, wk2, ok);
@@ -257,7 +340,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
                 wLn[v] = wk1[v] + R(HALF<LIM>) * s1;
             }
             riemann<RS, R>(wLz, wR, gammaR, igm1R, Fhi);
-            put_plane(nxt, wk1, Gn, RS != 3 ? 0 : 1 + cur);
+            put_own(nxt, wk1);
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
                 wLz[v] = wLn[v];
@@ -265,55 +348,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
                 wk1[v] = wk2[v];
             }
         }
-
-        // (B) x and y faces of plane k: tasks [0, 272) x, [272, 544) y; every
-        // lane takes tasks tt and tt + 256, lanes with tt < 32 also tt + 512
-        auto face_task = [&](int t) {
-            const int d = t >= NXF;
-            const int u = t - NXF * d;
-            int base, st;
-            if (!d) {
-                const int jj = u / 17, fi = u - 17 * jj;
-                base = (jj + 2) * PW + fi;
-                st = 1;
-            } else {
-                base = (u >> 4) * PW + (u & 15) + 2;
-                st = PW;
-            }
-            R c[4][NV];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int p = base + s * st;
-                c[s][0] = sP[cur][0][p];
-                c[s][1] = sP[cur][1 + d][p];
-                c[s][2] = sP[cur][2 - d][p];
-                c[s][3] = sP[cur][3][p];
-                c[s][4] = sP[cur][4][p];
-            }
-            R wL[NV], wR[NV], F[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                R s0, s1;
-                half_slopes<LIM>(c[1][v] - c[0][v], c[2][v] - c[1][v], c[3][v] - c[2][v], s0, s1);
-                wL[v] = c[1][v] + R(HALF<LIM>) * s0;
-                wR[v] = c[2][v] - R(HALF<LIM>) * s1;
-            }
-            riemann<RS, R>(wL, wR, gammaR, igm1R, F);
-            sF[cur][0][t] = F[0];
-            sF[cur][1][t] = d ? F[2] : F[1];
-            sF[cur][2][t] = d ? F[1] : F[2];
-            sF[cur][3][t] = F[3];
-            sF[cur][4][t] = F[4];
-        };
-        face_task(tt);
-        face_task(tt + 256);
-        if (tt < NTASK - 512) face_task(tt + 512);
-        // U^n of plane k (its load crosses the barrier; issued here it is not
-        // live during the face work)
-        if (!FIRST) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) Un[v] = load_un(a.Un + blk + v * CELLS + k * 256 + colp);
-        }
+        if (role < 2) put_ghost(nxt, G);
         __syncthreads();
 
         // (C) divergence, stage combination, stores of plane k
@@ -321,24 +356,25 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
             const double fz[NV] = {double(Fhi[0]) - double(Flo[0]), double(Fhi[2]) - double(Flo[2]),
                                    double(Fhi[3]) - double(Flo[3]), double(Fhi[1]) - double(Flo[1]),
                                    double(Fhi[4]) - double(Flo[4])};
-            const size_t cell = size_t(k) * 256 + colp;
             double out[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                const double dfx = double(sF[cur][v][j * 17 + i + 1]) - double(sF[cur][v][j * 17 + i]);
-                const double dfy = double(sF[cur][v][NXF + (j + 1) * 16 + i]) - double(sF[cur][v][NXF + j * 16 + i]);
-                const double L = -((dfx + dfy) + fz[v]) * inv_dx;
-                if (KIND == 1) out[v] = C0[v] + dt * L;
-                else if (KIND == 3) out[v] = 0.75 * Un[v] + 0.25 * (C0[v] + dt * L);
-                else if (KIND == 4) out[v] = (1.0 / 3.0) * Un[v] + (2.0 / 3.0) * (C0[v] + dt * L);
-                else out[v] = 0.5 * (Un[v] + (C0[v] + dt * L));
-                store_out(a.Uout + blk + v * CELLS + cell, out[v]);
+                const R xt = sF[cur][v][FX + j * NFX + i + 1];
+                const double dfx = double(xt) - double(Fx[v]);
+                const double dfy = double(sF[cur][v][colp + BN]) - double(Fy[v]);
+                const double u1 = C0[v] - dtdx * ((dfx + dfy) + fz[v]);   // input + dt L
+                if (KIND == 1) out[v] = u1;
+                else if (KIND == 3) out[v] = 0.75 * Un[v] + 0.25 * u1;
+                else if (KIND == 4) out[v] = (1.0 / 3.0) * Un[v] + (2.0 / 3.0) * u1;
+                else out[v] = 0.5 * (Un[v] + u1);
+                __builtin_nontemporal_store(out[v], uniform_at(a.Uout + blk + v * CELLS, cell8));
             }
             if (i < 2 || i >= BN - 2) {
                 const int side = i >= BN - 2;
-                double *x = a.XEout + (size_t(b) * NV * 2 + side) * SLAB + k * 32 + j * 2 + (i - (side ? BN - 2 : 0));
+                const unsigned x8 = (side * SLAB + j * 2 + (i - (side ? BN - 2 : 0))) * 8 + k * 256;
 #pragma unroll
-                for (int v = 0; v < NV; ++v) store_out(x + v * 2 * SLAB, out[v]);
+                for (int v = 0; v < NV; ++v)
+                    __builtin_nontemporal_store(out[v], uniform_at(a.XEout + (size_t(b) * NV + v) * 2 * SLAB, x8));
             }
             if (LAST) {
                 const bool skip = ((cf & 1) && i == 0) || ((cf & 2) && i == BN - 1) || ((cf & 4) && j == 0) ||
@@ -350,38 +386,20 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
                 if (!skip && sb > smax) smax = sb;
             }
         }
-        // flux registers of the x / y boundary faces of plane k
-        if (tid < 32) {
-            const int lane = tid & 15;
-            const int fs = tid < 16 ? D.freg[0] : D.freg[2];   // -x / -y face register
-            const int gs = tid < 16 ? D.freg[1] : D.freg[3];   // +x / +y face register
-            const int lo = tid < 16 ? lane * 17 : NXF + lane;
-            const int hi = tid < 16 ? lane * 17 + 16 : NXF + BN * 16 + lane;
-            if (fs >= 0) {
-                double *r = a.freg + size_t(fs) * NV * REG + k * 16 + lane;
+        // flux registers of the lower x / y boundary faces of plane k (the
+        // upper ones are kept by the extra task)
+        if (D.freg[0] >= 0 && i == 0) keep(D.freg[0], k * 16 + j, Fx[0], Fx[1], Fx[2], Fx[3], Fx[4]);
+        if (D.freg[2] >= 0 && j == 0) keep(D.freg[2], k * 16 + i, Fy[0], Fy[1], Fy[2], Fy[3], Fy[4]);
 #pragma unroll
-                for (int v = 0; v < NV; ++v) r[v * REG] = double(sF[cur][v][lo]);
-            }
-            if (gs >= 0) {
-                double *r = a.freg + size_t(gs) * NV * REG + k * 16 + lane;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) r[v * REG] = double(sF[cur][v][hi]);
-            }
-        }
-        // slide the conserved ring and the prefetched ghosts
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
+        for (int v = 0; v < NV; ++v) {   // slide the conserved ring
             C0[v] = C1[v];
             C1[v] = C2[v];
-            C2[v] = Cn[v];
-            if (gl) Gn[v] = Gn2[v];
             Flo[v] = Fhi[v];
         }
     };
     if (sizeof(R) == 8) {
         // two planes per trip (slabs have an even number of planes, starting
-        // at an even plane): the register ring then needs about half the
-        // moves, 6% fewer instructions per plane
+        // at an even plane): the register ring then needs about half the moves
         for (int k = k0; k < k1; k += 2) {
             __builtin_assume((k & 1) == 0);
             plane(k);
@@ -393,11 +411,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
         for (int k = k0; k < k1; ++k) plane(k);
     }
     // flux register of the +z face (Flo holds the flux of face 15+1/2)
-    if (k1 == BN && D.freg[5] >= 0) {
-        double *r = a.freg + size_t(D.freg[5]) * NV * REG + colp;
-        r[0] = double(Flo[0]); r[REG] = double(Flo[2]); r[2 * REG] = double(Flo[3]);
-        r[3 * REG] = double(Flo[1]); r[4 * REG] = double(Flo[4]);
-    }
+    if (k1 == BN && D.freg[5] >= 0) keep(D.freg[5], colp, Flo[0], Flo[2], Flo[3], Flo[1], Flo[4]);
     if (!ok) atomicOr(&mp.flags, 1);
     if (LAST) {
         smax = wave_max_u64(smax);
