@@ -54,3 +54,32 @@ def test_step_in_every_flux_regime(agile, flow, solver, limiter):
     o.step(dt)
     assert parity_error(U, o.state(), w.gamma).max() <= TOL_FP64
     m.close()
+
+
+# 2^-300: outside the range of the short division and square root of the
+# signal rate; mixed: ordinary and extreme blocks in one mesh
+@pytest.mark.parametrize("scale", ["ordinary", "extreme", "mixed"])
+@pytest.mark.parametrize("physics", ["euler", "mhd"])
+def test_dt_of_every_magnitude_is_the_oracles(agile, physics, scale):
+    """The CFL dt after an upload and, against an upload of the same state,
+    after a step (the last stage's and the flux correction's own signal)."""
+    blocks = W.refine_blocks(W.uniform_blocks((2, 2, 2)), [5])
+    w = (W.smooth_random(blocks, (2, 2, 2), 2, seed=2) if physics == "euler"
+         else W.mhd_smooth_random(blocks, (2, 2, 2), 2, seed=2))
+    f = {"ordinary": 1.0, "extreme": 2.0 ** -300, "mixed": None}[scale]
+    if f is None:       # every value of the even blocks' densities and energies kept, the odd ones' velocity zero
+        w.U[1::2, 1:4] = 0.0
+        if physics == "mhd":
+            w.U[1::2, 5:9] = 0.0
+    else:               # a change of units of mass: rho, m, e by f, B and psi by sqrt(f)
+        w.U[:, :5] *= f
+        if physics == "mhd":
+            w.U[:, 5:] *= f ** 0.5
+    o = Oracle(w)
+    m = agile.Mesh.from_workload(w)
+    assert m.dt() == o.dt()
+    m.step_cfl(1)
+    after = m.dt()
+    w.U = m.readback()
+    assert Oracle(w).dt() == after
+    m.close()
