@@ -5,9 +5,13 @@
 // Morton order of the block coordinates, the space-filling-curve walk of the
 // main update loop in Sec. 2.1.3):
 //   U[2]   [block][var][16][16][16]   interiors only; stage input / output
-//   XE[2]  [block][var][side][16][16][2]
+//   XE[2]  [block][plane k][side][var][row j][2]
 //          copy of the two x-boundary columns of each row (side 0: i = 0,1;
-//          side 1: i = 14,15) so that x-ghosts read whole 256-byte runs
+//          side 1: i = 14,15) so that x-ghosts read whole runs.  A plane's
+//          values of both sides and all variables stand together: the stages
+//          march over k in step in all blocks, and with k inside [side][var]
+//          the accesses of a moment lay 256 bytes each at multiples of 4 KiB
+//          (FP32-flux stages of 1856 blocks 183 / 215 -> 176 / 210 us)
 //   halo   [slot][var][512]            ghost slabs of faces at a level jump
 //   freg   [slot][var][256]            face fluxes kept for flux correction
 // A ghost slab is 2 cells deep, stored in (k, j, i) order of the ghost box:
@@ -59,6 +63,11 @@ struct MeshParams {
     int flags;               // bit 0: non-physical state met
     int physics;             // AGILE_EULER, AGILE_MHD_GLM or AGILE_SRHD
 };
+
+// Index in XE of row 0 of plane k, side and variable of a block with NV variables.
+__host__ __device__ inline size_t xe_index(int NV, size_t block, int k, int side, int v) {
+    return (((block * BN + k) * 2 + side) * NV + v) * (BN * NG);
+}
 
 // Index of ghost cell (layer g, tangential coordinates (ta, tb) in axis
 // order) in the 512-cell slab of a face normal to axis d.

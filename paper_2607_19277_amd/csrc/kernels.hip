@@ -62,7 +62,7 @@ __device__ __forceinline__ double block_value_xe(const BlockDesc *desc, const do
         }
         if (xx < NG || xx >= BN - NG) {
             const int side = xx >= BN - NG;
-            return XE[((size_t(b) * NV + v) * 2 + side) * SLAB + (z * 16 + y) * 2 + (xx - (side ? BN - NG : 0))];
+            return XE[xe_index(NV, b, z, side, v) + y * 2 + (xx - (side ? BN - NG : 0))];
         }
     }
     return block_value(desc, U, halo, NV, C, v, x, y, z);
@@ -328,7 +328,7 @@ __device__ __forceinline__ void reflux_block(const RefluxTask *__restrict__ t, M
             U[(size_t(block) * NV + v) * CELLS + cell] = nu[v];
             if (XE && (cx < 2 || cx >= BN - 2)) {
                 const int xs = cx >= BN - 2;
-                XE[((size_t(block) * NV + v) * 2 + xs) * SLAB + (cz * 16 + cy) * 2 + (cx - (xs ? BN - 2 : 0))] = nu[v];
+                XE[xe_index(NV, block, cz, xs, v) + cy * 2 + (cx - (xs ? BN - 2 : 0))] = nu[v];
             }
         }
         if (last) {
@@ -390,11 +390,11 @@ __global__ __launch_bounds__(256) void k_reflux_restrict(const RefluxTask *__res
 __global__ __launch_bounds__(256) void k_xexport(const double *U, double *XE, int first, int NV) {
     const int b = first + blockIdx.x;
     for (int e = threadIdx.x; e < NV * XE_CELLS; e += blockDim.x) {
-        const int v = e / XE_CELLS, r = e - v * XE_CELLS;
-        const int side = r / SLAB, s = r - side * SLAB;
-        const int g = s & 1, row = s >> 1;   // row = k*16 + j
-        const int x = side ? BN - 2 + g : g;
-        XE[(size_t(b) * NV + v) * XE_CELLS + r] = U[(size_t(b) * NV + v) * CELLS + row * 16 + x];
+        const int c = e & 31, run = e >> 5;   // run = (k * 2 + side) * NV + v
+        const int v = run % NV, ks = run / NV;
+        const int row = (ks >> 1) * 16 + (c >> 1);
+        const int x = (ks & 1 ? BN - 2 : 0) + (c & 1);
+        XE[size_t(b) * NV * XE_CELLS + e] = U[(size_t(b) * NV + v) * CELLS + row * 16 + x];
     }
 }
 

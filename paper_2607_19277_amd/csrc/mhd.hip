@@ -140,15 +140,15 @@ void k_mhd_stage(SweepArgs a) {
     const int gnb = Dsc->nb[gf];
     // lanes of the two x-boundary columns also write the x-boundary copy
     const bool xcol = i < NG || i >= BN - NG;
-    double *const xo = a.XEout + (size_t(b) * NV * 2 + (i >= BN - NG)) * SLAB + j * 2 + (i >= BN - NG ? i - (BN - NG) : i);
+    double *const xo = a.XEout + xe_index(NV, b, 0, i >= BN - NG, 0) + j * 2 + (i >= BN - NG ? i - (BN - NG) : i);
     auto gload = [&](int k, double G[NV]) {
         const double *src;
         int st;
         if (gnb >= 0 && gd == 0) {
             // x ghosts: the neighbour's boundary columns from its x-boundary
             // copy (whole 256-byte runs instead of 16 bytes of each row)
-            src = a.XEin + (size_t(gnb) * NV * 2 + (gside ? 0 : 1)) * SLAB + (k * 16 + gy) * 2 + ggl;
-            st = 2 * SLAB;
+            src = a.XEin + xe_index(NV, gnb, k, gside ? 0 : 1, 0) + gy * 2 + ggl;
+            st = BN * NG;
         } else if (gnb >= 0) {
             const int yn = gside ? gp - BN : gp + BN;
             src = a.Uin + size_t(gnb) * NV * CELLS + (k * 16 + yn) * 16 + gx;
@@ -330,7 +330,7 @@ void k_mhd_stage(SweepArgs a) {
                 else out[v] = 0.5 * (Un[v] + (C0[v] + dt * L));
                 if (STAGE == 2 && v == 8 && !skip) out[v] = out[v] * fdec;
                 store_out(a.Uout + cell + size_t(v) * CELLS, out[v]);
-                if (xcol) store_out(xo + size_t(k) * 32 + v * 2 * SLAB, out[v]);   // the x-boundary copy
+                if (xcol) store_out(xo + k * (2 * NV * BN * NG) + v * (BN * NG), out[v]);   // the x-boundary copy
             }
             gload(min(k + 1, BN - 1), G);
             if (STAGE == 2) {
@@ -405,7 +405,6 @@ __global__ __launch_bounds__(256) void k_glm_decay(const BlockDesc *desc, MeshPa
     const double h = hfrac * P.dt;
     const double f = exp(-h * P.ch * P.glm_alpha * inv_dx);
     v2d *psi = reinterpret_cast<v2d *>(U + (size_t(b) * NV + 8) * CELLS);
-    double *xe = XE ? XE + (size_t(b) * NV + 8) * 2 * SLAB : nullptr;
 #pragma unroll
     for (int r = 0; r < CELLS / 512; ++r) {
         const int q = threadIdx.x + 256 * r;   // cells 2q, 2q + 1: pair q & 7 of row q >> 3 (row = k * 16 + j)
@@ -414,7 +413,7 @@ __global__ __launch_bounds__(256) void k_glm_decay(const BlockDesc *desc, MeshPa
         x.y *= f;
         __builtin_nontemporal_store(x, psi + q);
         const int ip = q & 7;
-        if (xe && (ip == 0 || ip == 7)) *reinterpret_cast<v2d *>(xe + (ip == 7) * SLAB + (q >> 3) * 2) = x;
+        if (XE && (ip == 0 || ip == 7)) *reinterpret_cast<v2d *>(XE + xe_index(NV, b, q >> 7, ip == 7, 8) + ((q >> 3) & 15) * 2) = x;
     }
 }
 

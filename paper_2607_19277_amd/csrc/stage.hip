@@ -79,6 +79,7 @@ __device__ __forceinline__ void to_prim_z(const double C[NV], double gamma, doub
 // registers, so that the five variables of a cell cost one address
 // computation between them (the compiler would add the variable's stride to
 // 64-bit lane addresses).
+typedef double double2v __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) double gdouble;
 typedef __attribute__((address_space(1))) char gchar;
 __device__ __forceinline__ gdouble *uniform_at(const double *base, unsigned off) {
@@ -106,7 +107,9 @@ __device__ __forceinline__ gdouble *uniform_at(const double *base, unsigned off)
 // blocks: 263 -> 210 us).  Not faster: three waves per SIMD (168 registers;
 // the face work then spills or loses its instruction-level parallelism, 2-15%
 // slower), the upper faces of 8 planes at once from global memory (balanced
-// over the waves, 4% slower), cells loaded one plane further ahead (equal).
+// over the waves, 4% slower), cells or ghosts loaded one plane further ahead
+// (equal, or up to 3% slower).  On noisy data (256^3 shear layer) the clock drops from 2.39 to
+// 2.04 GHz under this kernel, so there operations cost their energy too.
 // KIND: 1 first stage (U1 = U + dt L), 2 last SSP-RK2 stage
 // ((U^n + (U1 + dt L))/2), 3 middle SSP-RK3 stage (3/4 U^n + 1/4 (U1 + dt L)),
 // 4 last SSP-RK3 stage (1/3 U^n + 2/3 (U2 + dt L)).  The last stage of a step
@@ -118,7 +121,9 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
     // that one barrier per plane separates producers from consumers
     __shared__ R sP[2][NV][PLANE];
     __shared__ R sF[2][NV][NFACE];
-    __shared__ unsigned long long sMax[4];
+    // the x-boundary columns of a plane's output, as they stand in XE; stored
+    // by consecutive lanes after the next plane's barrier
+    __shared__ double sXE[2][2 * NV * BN * NG];
 
     // work item = (block, slab of kslab planes)
     const int nslab = BN / a.kslab;
@@ -175,9 +180,9 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
             gks = 32;
             gst = SLAB;
         } else if (gf < 2) {
-            gsrc = a.XEin + (size_t(nb) * NV * 2 + (gf == 0 ? 1 : 0)) * SLAB + gr;
-            gks = 32;
-            gst = 2 * SLAB;
+            gsrc = a.XEin + xe_index(NV, nb, 0, gf == 0 ? 1 : 0, 0) + gr;
+            gks = 2 * NV * BN * NG;
+            gst = BN * NG;
         } else {
             gsrc = a.Uin + size_t(nb) * NV * CELLS + (gf == 2 ? 224 : 0) + gr;
             gks = 256;
@@ -219,6 +224,17 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
     auto keep = [&](int slot, int pos, R f0, R f1, R f2, R f3, R f4) {
         double *r = a.freg + size_t(slot) * NV * REG + pos;
         r[0] = double(f0); r[REG] = double(f1); r[2 * REG] = double(f2); r[3 * REG] = double(f3); r[4 * REG] = double(f4);
+    };
+
+    // output plane k's x-boundary columns from LDS to XE: 16 bytes per lane,
+    // one run of 2560 bytes (stored by their own lanes they were five
+    // stores of 64-byte pieces per wave; ten steps of 1856 blocks 5437 -> 5360
+    // us, with FP32 fluxes 4977 -> 4885 us)
+    const int xpos = (i < NG ? i : NV * BN * NG + i - (BN - NG)) + j * NG;
+    auto export_x = [&](int k) {
+        if (tid < NV * BN * NG)
+            __builtin_nontemporal_store(reinterpret_cast<const double2v *>(sXE[k & 1])[tid],
+                                        reinterpret_cast<double2v *>(a.XEout + xe_index(NV, b, k, 0, 0)) + tid);
     };
 
     // ---- prologue: cells k0-2 .. k0+1 of the column, face k0-1/2, plane k0 in
@@ -369,12 +385,10 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
                 else out[v] = 0.5 * (Un[v] + u1);
                 __builtin_nontemporal_store(out[v], uniform_at(a.Uout + blk + v * CELLS, cell8));
             }
+            if (k > k0) export_x(k - 1);
             if (i < 2 || i >= BN - 2) {
-                const int side = i >= BN - 2;
-                const unsigned x8 = (side * SLAB + j * 2 + (i - (side ? BN - 2 : 0))) * 8 + k * 256;
 #pragma unroll
-                for (int v = 0; v < NV; ++v)
-                    __builtin_nontemporal_store(out[v], uniform_at(a.XEout + (size_t(b) * NV + v) * 2 * SLAB, x8));
+                for (int v = 0; v < NV; ++v) sXE[cur][xpos + v * (BN * NG)] = out[v];
             }
             if (LAST) {
                 const bool skip = ((cf & 1) && i == 0) || ((cf & 2) && i == BN - 1) || ((cf & 4) && j == 0) ||
@@ -412,8 +426,11 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
     }
     // flux register of the +z face (Flo holds the flux of face 15+1/2)
     if (k1 == BN && D.freg[5] >= 0) keep(D.freg[5], colp, Flo[0], Flo[2], Flo[3], Flo[1], Flo[4]);
+    __syncthreads();
+    export_x(k1 - 1);
     if (!ok) atomicOr(&mp.flags, 1);
     if (LAST) {
+        unsigned long long *sMax = reinterpret_cast<unsigned long long *>(sP);   // no longer read
         smax = wave_max_u64(smax);
         if ((tid & 63) == 0) sMax[tid >> 6] = smax;
         __syncthreads();
