@@ -138,8 +138,29 @@ struct StageArgs {
 // A stage's output and U^n are each touched once per launch: their accesses
 // carry streaming (nontemporal) hints so that they do not displace, in L2, the
 // input planes and ghost rows that neighbouring work items read again.
-__device__ __forceinline__ void store_out(double *p, double v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ double load_un(const double *p) { return __builtin_nontemporal_load(p); }
+// A value at a wave-uniform base plus a lane offset in bytes: base in scalar
+// registers, so that the variables of a cell cost one address
+// computation between them (the compiler would add the variable's stride to
+// 64-bit lane addresses).
+typedef double double2v __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) double gdouble;
+typedef __attribute__((address_space(1))) char gchar;
+__device__ __forceinline__ gdouble *uniform_at(const double *base, unsigned off) {
+    gchar *b = (gchar *)base;
+    asm("" : "+s"(b));
+    return (gdouble *)(b + off);
+}
+
+typedef __attribute__((address_space(1))) double2v gdouble2v;
+__device__ __forceinline__ gdouble2v *uniform2_at(const double *base, unsigned off) {
+    return (gdouble2v *)uniform_at(base, off);
+}
+// x, computed anew where it stands: keeps what follows from it (the addresses
+// of rarely taken branches above all) out of registers held across a loop
+__device__ __forceinline__ int opaque(int x) {
+    asm("" : "+v"(x));
+    return x;
+}
 
 // The ideal-MHD stage (nvar 9) of the listed blocks.
 struct SweepArgs {
@@ -156,6 +177,7 @@ struct SweepArgs {
     unsigned long long *cmax;  // per block, as smax, for max_d (|v_d| + c_f,d)
     const int *list;
     int nblocks;
+    int kslab;             // planes per workgroup: 16, 8 or 4 (same arithmetic per cell)
 };
 
 } // namespace agile

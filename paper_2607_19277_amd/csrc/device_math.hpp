@@ -654,8 +654,10 @@ __device__ __forceinline__ double mhd_signal(const double U[9], double gamma, do
 // a = max(S_R, 0), b = min(S_L, 0).  Physical flux along n: mass rho u_n,
 // momentum rho u u_n + (p + B^2/2) e_n - B B_n, energy
 // u_n (e + p + B^2/2) - B_n (u.B), induction u_n B - B_n u.
-template <typename R>
-__device__ __forceinline__ void mhd_hll(const R wL[9], const R wR[9], R gamma, R igm1, R ch, R inv2ch, R F[9]) {
+// FP32: the operations in the order of these formulas (see riemann_euler).
+__device__ __forceinline__ void mhd_hll(const float wL[9], const float wR[9], float gamma, float igm1, float ch,
+                                        float inv2ch, float F[9]) {
+    using R = float;
     const R bn = R(0.5) * (wL[5] + wR[5]) - (wR[8] - wL[8]) * inv2ch;
     const R ps = R(0.5) * (wL[8] + wR[8]) - R(0.5) * ch * (wR[5] - wL[5]);
     R U[2][9], Fs[2][9], c[2];
@@ -695,6 +697,59 @@ __device__ __forceinline__ void mhd_hll(const R wL[9], const R wR[9], R gamma, R
         F[v] = ((ap * Fs[0][v] - bm * Fs[1][v]) + ab * (U[1][v] - U[0][v])) * inv;
     }
     F[5] = ps;
+    F[8] = ch * ch * bn;
+}
+
+// FP64: the same flux with F = u U + Phi for either side, Phi the pressure,
+// tension and induction terms, so that with al = S_R+/(S_R+ - S_L-),
+// be = -S_L-/(S_R+ - S_L-), a = al (u_L - S_L-), b = be (u_R - S_R+)
+//   F = a U_L + b U_R + al Phi_L + be Phi_R
+// and neither U nor F of a side is formed (the terms in B_n^2 carry
+// al + be = 1).  Fast speed without division: with x = gamma p + B^2 and
+// D = sqrt(x^2 - 4 gamma p B_n^2), c_f = sqrt((x + D)/(2 rho)) =
+// (x + D)/sqrt(2 (x + D) rho); D^2 is kept above 1e-40 x^2, where D no longer
+// counts, instead of 0.
+__device__ __forceinline__ double mhd_fast_speed(double rho, double gp, double bb, double bn2) {
+    const double x = gp + bb, x2 = x * x;
+    const double q = __builtin_fmax(fma(-4.0 * gp, bn2, x2), 1e-40 * x2);
+    const double y = __builtin_amdgcn_rsq(q), d = q * y;
+    const double z = x + fma(0.5 * d, fma(-d, y, 1.0), d);
+    const double s = (z + z) * rho;
+    const double r = __builtin_amdgcn_rsq(s), c = z * r;
+    return fma(0.5 * c, fma(-s * r, r, 1.0), c);
+}
+__device__ __forceinline__ void mhd_hll(const double wL[9], const double wR[9], double gamma, double igm1, double ch,
+                                        double inv2ch, double F[9]) {
+    const double bn = fma(0.5, wL[5] + wR[5], (wL[8] - wR[8]) * inv2ch);
+    const double uL = wL[1], uR = wR[1];
+    const double bn2 = bn * bn;
+    const double bbL = fma(wL[7], wL[7], fma(wL[6], wL[6], bn2));
+    const double bbR = fma(wR[7], wR[7], fma(wR[6], wR[6], bn2));
+    const double cL = mhd_fast_speed(wL[0], gamma * wL[4], bbL, bn2);
+    const double cR = mhd_fast_speed(wR[0], gamma * wR[4], bbR, bn2);
+    const double sr = __builtin_fmax(__builtin_fmax(uL + cL, uR + cR), 0.0);
+    const double sl = __builtin_fmin(__builtin_fmin(uL - cL, uR - cR), 0.0);
+    const double inv = rcp64(sr - sl);
+    const double al = sr * inv, be = -sl * inv;
+    const double a = al * (uL - sl), b = be * (uR - sr);
+    const double A = a * wL[0], B = b * wR[0];
+    const double ptL = fma(0.5, bbL, wL[4]), ptR = fma(0.5, bbR, wR[4]);
+    const double m1 = fma(al, wL[6], be * wR[6]), m2 = fma(al, wL[7], be * wR[7]);   // mean fields
+    const double n1 = fma(al, wL[2], be * wR[2]), n2 = fma(al, wL[3], be * wR[3]);   // and velocities
+    F[0] = A + B;
+    F[1] = fma(A, uL, B * uR) + fma(-bn, bn, fma(al, ptL, be * ptR));
+    F[2] = fma(A, wL[2], fma(B, wR[2], -bn * m1));
+    F[3] = fma(A, wL[3], fma(B, wR[3], -bn * m2));
+    F[6] = fma(a, wL[6], fma(b, wR[6], -bn * n1));
+    F[7] = fma(a, wL[7], fma(b, wR[7], -bn * n2));
+    const double vvL = fma(wL[3], wL[3], fma(wL[2], wL[2], uL * uL));
+    const double vvR = fma(wR[3], wR[3], fma(wR[2], wR[2], uR * uR));
+    const double vbL = fma(wL[3], wL[7], fma(wL[2], wL[6], uL * bn));
+    const double vbR = fma(wR[3], wR[7], fma(wR[2], wR[6], uR * bn));
+    const double eL = fma(0.5, bbL, wL[4] * igm1), eR = fma(0.5, bbR, wR[4] * igm1);
+    const double fL = fma(-bn, vbL, uL * ptL), fR = fma(-bn, vbR, uR * ptR);
+    F[4] = fma(0.5, fma(A, vvL, B * vvR), fma(a, eL, b * eR)) + fma(al, fL, be * fR);
+    F[5] = 0.5 * fma(-ch, wR[5] - wL[5], wL[8] + wR[8]);
     F[8] = ch * ch * bn;
 }
 

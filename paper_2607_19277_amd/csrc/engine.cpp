@@ -618,6 +618,7 @@ int Engine::enqueue_stage(int kind, int in, int out, double bw, bool fill, std::
         m.cmax = cmax_;
         m.list = d_list_;
         m.nblocks = nlist_;
+        m.kslab = auto_kslab();
         TIMED(AGILE_K_STAGE, launch_mhd_stage(m, kind, cfg_.precision, st));
         return enqueue_correct(out, bw, last, fill, err);
     }

@@ -75,19 +75,6 @@ __device__ __forceinline__ void to_prim_z(const double C[NV], double gamma, doub
     w[0] = R(q[0]); w[1] = R(q[3]); w[2] = R(q[1]); w[3] = R(q[2]); w[4] = R(q[4]);
 }
 
-// A value at a wave-uniform base plus a lane offset in bytes: base in scalar
-// registers, so that the five variables of a cell cost one address
-// computation between them (the compiler would add the variable's stride to
-// 64-bit lane addresses).
-typedef double double2v __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(1))) double gdouble;
-typedef __attribute__((address_space(1))) char gchar;
-__device__ __forceinline__ gdouble *uniform_at(const double *base, unsigned off) {
-    gchar *b = (gchar *)base;
-    asm("" : "+s"(b));
-    return (gdouble *)(b + off);
-}
-
 } // namespace
 
 #ifndef AGILE_STAGE_WAVES_F64

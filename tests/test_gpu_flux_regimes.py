@@ -9,7 +9,7 @@ import pytest
 
 from oracle.oracle import Oracle
 from paper_2607_19277_amd import workloads as W
-from parity import TOL_FP64, parity_error
+from parity import TOL_FP64, parity_error, parity_error_mhd
 
 pytestmark = pytest.mark.gpu
 
@@ -53,6 +53,44 @@ def test_step_in_every_flux_regime(agile, flow, solver, limiter):
     U = m.readback()
     o.step(dt)
     assert parity_error(U, o.state(), w.gamma).max() <= TOL_FP64
+    m.close()
+
+
+# MHD: bulk velocity, factor of the smooth velocities, factor of the smooth
+# field, uniform field added
+MHD_FLOWS = {"+x": ((4.0, 0, 0), 1.0, 1.0, (0, 0, 0)), "-z": ((0, 0, -4.0), 1.0, 1.0, (0, 0, 0)),
+             "mixed": ((0, 0, 0), 12.0, 1.0, (0, 0, 0)), "no field": ((0, 0, 0), 1.0, 0.0, (0, 0, 0)),
+             "strong y field": ((0, 0, 0), 1.0, 1.0, (0, 3.0, 0)), "rest": ((0, 0, 0), 0.0, 0.0, (0.5, 0, 0))}
+
+
+def _mhd_workload(flow):
+    w = W.mhd_smooth_random(W.refine_blocks(W.uniform_blocks((2, 2, 2)), [3]), (2, 2, 2), 2, seed=6)
+    bulk, fv, fb, b0 = MHD_FLOWS[flow]
+    rho = w.U[:, 0]
+    u = w.U[:, 1:4] / rho[:, None]
+    B = w.U[:, 5:8]
+    p = (w.gamma - 1.0) * (w.U[:, 4] - 0.5 * rho * (u * u).sum(axis=1) - 0.5 * (B * B).sum(axis=1))
+    v = [bulk[d] + fv * u[:, d] for d in range(3)]
+    w.U = W.prim_to_cons(w.gamma, rho, *v, p, B=[b0[d] + fb * B[:, d] for d in range(3)], psi=0.01 * fb * B[:, 0])
+    return w
+
+
+@pytest.mark.parametrize("flow", list(MHD_FLOWS))
+def test_mhd_step_in_every_flux_regime(agile, flow):
+    w = _mhd_workload(flow)
+    o = Oracle(w)
+    dt = o.dt()
+    m = agile.Mesh.from_workload(w)
+    assert m.dt() == dt
+    m.step(dt)
+    U = m.readback()
+    o.step(dt)
+    R = o.state()
+    if flow in ("no field", "rest"):     # no scale for a field or psi that is zero: the hydrodynamic part, and zero
+        assert parity_error(U[:, :5], R[:, :5], w.gamma).max() <= TOL_FP64
+        assert abs(U[:, 5:] - R[:, 5:]).max() <= TOL_FP64
+    else:
+        assert parity_error_mhd(U, R, w.gamma).max() <= TOL_FP64
     m.close()
 
 
