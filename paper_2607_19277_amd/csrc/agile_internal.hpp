@@ -129,7 +129,7 @@ struct StageArgs {
     unsigned long long *smax;  // per block: reset in stage 1, maximum in stage 2
     const int *list;       // blocks to update (pool indices), or null for [0, nblocks)
     int nblocks;           // number of blocks to update
-    int kslab;             // planes per workgroup: 16, 8 or 4 (same arithmetic per cell)
+    int kslab;             // planes per workgroup: 16, 8, 4 or 2 (same arithmetic per cell)
     int xcd;               // 1: XCD-aware workgroup -> block mapping
     int stage;             // stage kind: 1 first, 2 last SSP-RK2, 3 middle / 4 last SSP-RK3
     int limiter;           // 0 minmod, 1 van Leer
@@ -177,7 +177,7 @@ struct SweepArgs {
     unsigned long long *cmax;  // per block, as smax, for max_d (|v_d| + c_f,d)
     const int *list;
     int nblocks;
-    int kslab;             // planes per workgroup: 16, 8 or 4 (same arithmetic per cell)
+    int kslab;             // planes per workgroup: 16, 8, 4 or 2 (same arithmetic per cell)
 };
 
 } // namespace agile

@@ -989,7 +989,8 @@ int Engine::tune_launches(std::string &err, int max_blocks) {
     // which is free between steps: the same work as in a step, on a valid
     // state, with the mesh's state untouched.
     const int kinds[2] = {1, cfg_.rk == 3 ? 4 : 2};
-    int bk[2] = {stage_kslab(false), stage_kslab(true)}, bx[2] = {xcd, xcd_last};
+    const int now[2] = {stage_kslab(false), stage_kslab(true)};
+    int bk[2] = {now[0], now[1]}, bx[2] = {xcd, xcd_last};
     for (int t = 0; t < 2; ++t) {
         float best = 1e30f;
         std::vector<std::pair<int, int>> cand{{bk[t], bx[t]}};
@@ -1035,6 +1036,8 @@ int Engine::tune_launches(std::string &err, int max_blocks) {
     for (const MeshSlot &S : slots_)
         if (S.used && S.active) CHK(launch_smax(desc_, mp_, U_[0], smax_, cmax_, S.first, int(S.plan.n), nvar_, st));
     CHK(hipStreamSynchronize(st));
+    if (bk[0] == now[0]) bk[0] = kslab;   // the automatic depth stays automatic
+    if (bk[1] == now[1]) bk[1] = kslab_last;
     if (bk[0] != kslab || bx[0] != xcd || bk[1] != kslab_last || bx[1] != xcd_last) {
         kslab = bk[0];
         xcd = bx[0];

@@ -186,11 +186,28 @@ public:
     int xcd = 0;
     int kslab_last = 0;
     int xcd_last = 0;
-    // 16 planes per work item from 512 active blocks on (a whole round of the
-    // GPU's workgroup slots), 8 from 256, else 4: on a 64-block box 4-plane
-    // slabs make the step 2.4x faster, at 512 and more blocks 16 planes are
-    // within 1% of the fastest shape
-    int auto_kslab() const { return nlist_ >= 512 ? 16 : (nlist_ >= 256 ? 8 : 4); }
+    // Planes per work item from the number of active blocks.  A launch's time
+    // goes with the work items of the fullest of the 256 CUs times a work
+    // item's length, k planes and about 1.4 planes' worth of prologue, plus a
+    // part for ramp and tail: T(k) ~ ceil(blocks (16/k) / 256) (k + 1.4) + t(k),
+    // t = 8, 6.5, 5 planes for k = 16, 8, 4; the smallest T, the larger k on a
+    // tie.  Steps of uniform boxes (HLLC, us, k = 16 / 8 / 4): 64 blocks 84 / 54
+    // / 40, 180: 86 / 74 / 70, 294: 120 / 105 / 99, 343: 119 / 108 / 114, 448:
+    // 126 / 129 / 132, 576: 178 / 159 / 163, 810: 221 / 212 / 222, 1728: 402 /
+    // 415 / 455; FP32 flux, LF with van Leer and SRHD order alike.
+    int auto_kslab() const {
+        int best = 16;
+        double t = 0.0;
+        for (int k = 16; k >= 2; k /= 2) {
+            const int items = (nlist_ * (BN / k) + 255) / 256;
+            const double c = items * (k + 1.4) + (k == 16 ? 8.0 : (k == 8 ? 6.5 : (k == 4 ? 5.0 : 4.2)));
+            if (k == 16 || c < t - 1e-9) {
+                t = c;
+                best = k;
+            }
+        }
+        return best;
+    }
     int stage_kslab(bool last_kind) const {
         const int k = last_kind ? kslab_last : kslab;
         return k ? k : auto_kslab();

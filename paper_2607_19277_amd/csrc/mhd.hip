@@ -439,7 +439,7 @@ __global__ __launch_bounds__(256) void k_glm_decay(const BlockDesc *desc, MeshPa
 
 hipError_t launch_mhd_stage(const SweepArgs &a, int stage, int precision, hipStream_t s) {
     if (a.nblocks <= 0) return hipSuccess;
-    if (a.kslab != 16 && a.kslab != 8 && a.kslab != 4) return hipErrorInvalidValue;
+    if (a.kslab != 16 && a.kslab != 8 && a.kslab != 4 && a.kslab != 2) return hipErrorInvalidValue;
     const dim3 grid(a.nblocks * (BN / a.kslab)), block(256);
     if (precision == 0) {
         if (stage == 1) hipLaunchKernelGGL((k_mhd_stage<1, double>), grid, block, 0, s, a);

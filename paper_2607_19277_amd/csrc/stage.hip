@@ -431,7 +431,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
 
 hipError_t launch_stage(const StageArgs &a, int riemann, int precision, hipStream_t s) {
     if (a.nblocks <= 0) return hipSuccess;
-    if (a.kslab != 16 && a.kslab != 8 && a.kslab != 4) return hipErrorInvalidValue;
+    if (a.kslab != 16 && a.kslab != 8 && a.kslab != 4 && a.kslab != 2) return hipErrorInvalidValue;
     if (a.stage < 1 || a.stage > 4 || riemann < 0 || riemann > 3 || a.limiter < 0 || a.limiter > 1)
         return hipErrorInvalidValue;
     const dim3 grid(xcd_grid(a.nblocks * (BN / a.kslab), a.xcd)), block(256);

@@ -5,6 +5,7 @@ both limiters, on a mesh with a level jump.  One step from the same state to
 the FP64 bar of the repository (1e-12)."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 
 from oracle.oracle import Oracle
@@ -92,6 +93,30 @@ def test_mhd_step_in_every_flux_regime(agile, flow):
     else:
         assert parity_error_mhd(U, R, w.gamma).max() <= TOL_FP64
     m.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32flux"])
+@pytest.mark.parametrize("physics", ["euler", "srhd", "mhd"])
+def test_cells_do_not_depend_on_the_number_of_blocks(agile, physics, precision):
+    """A periodic state of 2^3 blocks repeated to 4^3, 6^3 and 8^3 blocks: the
+    stage then takes 2, 4, 8 and 16 planes per work item, and every copy must
+    hold the same bits after the same step."""
+    base = W.uniform_blocks((2, 2, 2))
+    w = {"euler": W.smooth_random, "srhd": W.srhd_smooth_random, "mhd": W.mhd_smooth_random}[physics](base, (2, 2, 2), 1, 5)
+    prec = agile.FP64 if precision == "fp64" else agile.FP32_FLUX
+    of = {tuple(r[1:]): q for q, r in enumerate(base.tolist())}
+    dt, first = Oracle(w).dt(), None
+    for n in (2, 4, 6, 8):
+        blocks = W.uniform_blocks((n, n, n))
+        src = np.array([of[tuple(c % 2 for c in r[1:])] for r in blocks.tolist()])
+        m = agile.Mesh(w.physics, w.riemann, prec, w.gamma, w.cfl, w.glm_alpha, (n, n, n), hi=(n / 2,) * 3)
+        m.set_blocks(blocks, w.U[src])
+        m.step(dt)
+        U = m.readback()
+        m.close()
+        if first is None:
+            first = U
+        assert np.array_equal(U, first[src]), (n, float(np.abs(U - first[src]).max()))
 
 
 # 2^-300: outside the range of the short division and square root of the
