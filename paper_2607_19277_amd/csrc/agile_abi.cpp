@@ -517,7 +517,7 @@ int agile_last_dt(agile_mesh *m, double *dt_out) {
         std::string s;
         int rc = m->eng->read_params(m->slot, hp, s);
         if (rc) return fail(m, rc, s);
-        *dt_out = hp.dt;
+        *dt_out = hp.last_dt;
         return AGILE_OK;
     });
 }

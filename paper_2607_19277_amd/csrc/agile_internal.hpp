@@ -53,11 +53,11 @@ struct MeshParams {
     double cfl;
     double inv_dx1;          // 1 / dx on level 1 (power-of-two scaling per level)
     double glm_alpha;
-    double dt;               // dt of the step in progress / last step
+    double dt;               // dt of the next step or the step in progress: cfl / smax, or as given
     double t;                // simulated time reached (sum of the dt of all steps)
-    double ch;               // MHD: GLM cleaning speed of the step in progress
+    double last_dt;          // dt of the last step
     unsigned long long smax; // bits of max signal rate of the current state
-    unsigned long long cmax; // MHD: bits of max_d (|v_d| + c_f,d) of the current state
+    unsigned long long cmax; // MHD: bits of max_d (|v_d| + c_f,d) of U^n, the GLM cleaning speed c_h of its step
     int first_block;         // block range of the mesh in the pool
     int nblocks;
     int flags;               // bit 0: non-physical state met

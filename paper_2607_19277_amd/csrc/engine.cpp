@@ -345,7 +345,7 @@ int Engine::add(const agile_config &cfg, Plan &&P, const double *u, int u_on_dev
     hp.nblocks = n;
     if (carry) {
         hp.t = carry->t;
-        hp.dt = carry->dt;
+        hp.last_dt = carry->last_dt;
         hp.flags = carry->flags;
     }
     auto undo = [&]() {
@@ -377,9 +377,8 @@ int Engine::add(const agile_config &cfg, Plan &&P, const double *u, int u_on_dev
                                hipMemcpyHostToDevice, st);
         }
     }
-    if (XE_[0]) e = e ? e : launch_xexport(U_[0], XE_[0], first, n, nvar_, st);
-    e = e ? e : launch_smax(desc_, mp_, U_[0], smax_, cmax_, first, n, nvar_, st);
-    e = e ? e : launch_mesh_reduce(mp_, d_meshes_ + cfg_.cap_meshes + s, 1, smax_, cmax_, 2, st);
+    e = e ? e : launch_smax(desc_, mp_, U_[0], XE_[0], smax_, cmax_, first, n, nvar_, st);
+    e = e ? e : launch_mesh_reduce(mp_, d_meshes_ + cfg_.cap_meshes + s, 1, smax_, cmax_, n, 0, st);
     e = e ? e : hipStreamSynchronize(st);
     if (e) {
         undo();
@@ -463,6 +462,8 @@ int Engine::rebuild(std::string &err) {
     CHK(hipStreamSynchronize(st));
     nlist_ = int(list.size());
     nmeshes_ = int(meshes.size());
+    nblocks_max_ = 0;
+    for (int q : meshes) nblocks_max_ = std::max(nblocks_max_, int(slots_[q].plan.n));
     nrestrict_ = int(res.size());
     nreflux_ = int(ref.size());
     // the flux correction and the restriction may share a launch when no
@@ -644,13 +645,10 @@ int Engine::enqueue_stage(int kind, int in, int out, double bw, bool fill, std::
     return enqueue_correct(out, bw, last, fill, err);
 }
 
-int Engine::enqueue_step(bool cfl_dt, std::string &err) {
+int Engine::enqueue_step(std::string &err) {
     const hipStream_t st = cfg_.stream;
     int e;
     const bool mhd = nvar_ == 9;
-    // CFL step: dt (and the GLM speed c_h) from the state's reductions; given
-    // dt: c_h only
-    if (cfl_dt || mhd) TIMED(AGILE_K_DT, launch_mesh_reduce(mp_, d_meshes_, nmeshes_, smax_, cmax_, cfl_dt ? 1 : 3, st));
     if (mhd) TIMED(AGILE_K_DT, launch_glm_decay(desc_, mp_, U_[0], XE_[0], d_list_, nlist_, 0.5, st));
     // Euler steps end with the ghost fill of their result (its restriction
     // shares the last flux correction's launch), so a step starts with valid
@@ -666,7 +664,7 @@ int Engine::enqueue_step(bool cfl_dt, std::string &err) {
     }
     // MHD: the second half of the psi decay is applied by the last stage and
     // its flux correction (k_mhd_stage<2>, k_reflux)
-    TIMED(AGILE_K_DT, launch_mesh_reduce(mp_, d_meshes_, nmeshes_, smax_, cmax_, 0, st));
+    TIMED(AGILE_K_DT, launch_mesh_reduce(mp_, d_meshes_, nmeshes_, smax_, cmax_, nblocks_max_, 1, st));
     ghosts_valid_ = !mhd;
     return AGILE_OK;
 }
@@ -695,7 +693,7 @@ int Engine::step_cfl(int nsteps, std::string &err) {
                 CHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
                 capturing_ = true;
                 std::string e2;
-                const int rc = enqueue_step(true, e2);
+                const int rc = enqueue_step(e2);
                 capturing_ = false;
                 hipGraph_t g = nullptr;
                 const hipError_t ec = hipStreamEndCapture(st, &g);
@@ -709,7 +707,7 @@ int Engine::step_cfl(int nsteps, std::string &err) {
             }
             CHK(hipGraphLaunch(graph_exec_, st));
         } else {
-            if ((e = enqueue_step(true, err))) return e;
+            if ((e = enqueue_step(err))) return e;
         }
         for (MeshSlot &S : slots_)
             if (S.used && S.active) S.steps_done++;
@@ -726,7 +724,7 @@ int Engine::step_dt(int s, double dt, std::string &err) {
         return AGILE_ESTATE;
     }
     CHK(launch_set_dt(mp_, s, dt, cfg_.stream));
-    if ((e = enqueue_step(false, err))) return e;
+    if ((e = enqueue_step(err))) return e;
     slots_[s].steps_done++;
     if (pairs_used_ > 4096) return tcollect(err);
     return AGILE_OK;
@@ -921,9 +919,9 @@ int Engine::tune(std::string &err, int max_blocks) {
     // state restored afterwards
     auto trial = [&](float &ms) -> int {
         ghosts_valid_ = false;
-        int rc = enqueue_step(true, e2);
+        int rc = enqueue_step(e2);
         if (!rc && hipEventRecord(t0, st) != hipSuccess) rc = AGILE_EDEVICE;
-        for (int r = 0; r < 3 && !rc; ++r) rc = enqueue_step(true, e2);
+        for (int r = 0; r < 3 && !rc; ++r) rc = enqueue_step(e2);
         if (!rc && hipEventRecord(t1, st) != hipSuccess) rc = AGILE_EDEVICE;
         if (!rc && hipEventSynchronize(t1) != hipSuccess) rc = AGILE_EDEVICE;
         if (!rc && hipEventElapsedTime(&ms, t0, t1) != hipSuccess) rc = AGILE_EDEVICE;
@@ -1034,7 +1032,7 @@ int Engine::tune_launches(std::string &err, int max_blocks) {
     (void)hipEventDestroy(t1);
     // restore the per-block signal maxima of the current state
     for (const MeshSlot &S : slots_)
-        if (S.used && S.active) CHK(launch_smax(desc_, mp_, U_[0], smax_, cmax_, S.first, int(S.plan.n), nvar_, st));
+        if (S.used && S.active) CHK(launch_smax(desc_, mp_, U_[0], nullptr, smax_, cmax_, S.first, int(S.plan.n), nvar_, st));
     CHK(hipStreamSynchronize(st));
     if (bk[0] == now[0]) bk[0] = kslab;   // the automatic depth stays automatic
     if (bk[1] == now[1]) bk[1] = kslab_last;

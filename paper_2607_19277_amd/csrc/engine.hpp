@@ -37,11 +37,10 @@ hipError_t launch_reflux(const RefluxTask *t, int n, MeshParams *mp, double *U, 
 hipError_t launch_reflux_restrict(const RefluxTask *rt, int nref, const RestrictTask *st, int nres, MeshParams *mp,
                                   double *U, double *XE, const double *freg, double *halo, unsigned long long *smax,
                                   unsigned long long *cmax, int NV, double bw, int last, hipStream_t s);
-hipError_t launch_xexport(const double *U, double *XE, int first, int n, int NV, hipStream_t s);
-hipError_t launch_smax(const BlockDesc *desc, MeshParams *mp, const double *U, unsigned long long *smax,
+hipError_t launch_smax(const BlockDesc *desc, MeshParams *mp, const double *U, double *XE, unsigned long long *smax,
                        unsigned long long *cmax, int first, int n, int NV, hipStream_t s);
 hipError_t launch_mesh_reduce(MeshParams *mp, const int *meshes, int nmesh, const unsigned long long *smax,
-                              const unsigned long long *cmax, int mode, hipStream_t s);
+                              const unsigned long long *cmax, int nmax, int end, hipStream_t s);
 hipError_t launch_mhd_stage(const SweepArgs &a, int stage, int precision, hipStream_t s);
 hipError_t launch_glm_decay(const BlockDesc *desc, MeshParams *mp, double *U, double *XE, const int *list,
                             int nblocks, double hfrac, hipStream_t s);
@@ -222,7 +221,7 @@ private:
     int enqueue_fill(int buf, std::string &err, bool restricted = false);
     int enqueue_correct(int out, double bw, bool last, bool fill, std::string &err);
     int enqueue_stage(int kind, int in, int out, double bw, bool fill, std::string &err);
-    int enqueue_step(bool cfl_dt, std::string &err);
+    int enqueue_step(std::string &err);
     int tbegin(int kind, std::string &err);
     int tend(int kind, std::string &err);
     int tcollect(std::string &err);
@@ -245,7 +244,7 @@ private:
     RestrictTask *d_restrict_ = nullptr;
     ProlongTask *d_prolong_ = nullptr;
     RefluxTask *d_reflux_ = nullptr;
-    int nlist_ = 0, nmeshes_ = 0, nrestrict_ = 0, nreflux_ = 0;
+    int nlist_ = 0, nmeshes_ = 0, nblocks_max_ = 0, nrestrict_ = 0, nreflux_ = 0;
     bool rr_indep_ = false;   // flux correction and restriction touch different blocks
     bool ghosts_valid_ = false;   // halo slabs hold the ghost fill of U[0] (Euler)
     std::vector<int> pro_off_, pro_cnt_;

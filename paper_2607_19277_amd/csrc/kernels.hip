@@ -276,7 +276,7 @@ __device__ __forceinline__ void reflux_block(const RefluxTask *__restrict__ t, M
     const double w = (bw * P.dt) * inv_dx;   // the stage's weight of dt L
     // psi decay factor of the second half step (MHD; the expression of k_glm_decay)
     const double hdec = 0.5 * P.dt;
-    const double fdec = NV == 9 ? exp(-hdec * P.ch * P.glm_alpha * inv_dx) : 1.0;
+    const double fdec = NV == 9 ? exp(-hdec * __longlong_as_double(P.cmax) * P.glm_alpha * inv_dx) : 1.0;
     unsigned long long m = 0, mc = 0;
     bool ok = true;
     // 256 lanes, one face cell each: (ta, tb) along the tangential axes,
@@ -386,32 +386,33 @@ __global__ __launch_bounds__(256) void k_reflux_restrict(const RefluxTask *__res
     }
 }
 
-// x-boundary columns of every row into XE, for pool blocks [first, first + n)
-__global__ __launch_bounds__(256) void k_xexport(const double *U, double *XE, int first, int NV) {
-    const int b = first + blockIdx.x;
-    for (int e = threadIdx.x; e < NV * XE_CELLS; e += blockDim.x) {
-        const int c = e & 31, run = e >> 5;   // run = (k * 2 + side) * NV + v
-        const int v = run % NV, ks = run / NV;
-        const int row = (ks >> 1) * 16 + (c >> 1);
-        const int x = (ks & 1 ? BN - 2 : 0) + (c & 1);
-        XE[size_t(b) * NV * XE_CELLS + e] = U[(size_t(b) * NV + v) * CELLS + row * 16 + x];
-    }
-}
-
-// per-block maximum signal rate (and, with cmax, the MHD speed max_d |v_d| +
-// c_f,d) of the current state, pool blocks [first, first + n)
-__global__ __launch_bounds__(256) void k_smax(const BlockDesc *desc, MeshParams *mp, const double *U,
-                                              unsigned long long *smax, unsigned long long *cmax, int first, int NV) {
+// After an upload, pool blocks [first, first + n): per-block maximum signal rate
+// (and, with cmax, the MHD speed max_d |v_d| + c_f,d) and the x-boundary columns
+// of every row into XE, from one read of the state.  A trip is a plane: lane =
+// cell (x, y), and the lanes at x = 0, 1, 14, 15 write the plane's runs of XE.
+// Bound by HBM on large meshes, as the copy of the columns by itself was, whose
+// rows share their cache lines with the rest of the state (512 to 2304 blocks 103 -> 47
+// us on average, 18944 MHD blocks 2747 -> 1430 us).
+template <int NV>
+__global__ __launch_bounds__(256) void k_smax(const BlockDesc *desc, MeshParams *mp, const double *__restrict__ U,
+                                              double *__restrict__ XE, unsigned long long *smax,
+                                              unsigned long long *cmax, int first) {
     __shared__ unsigned long long sMax[2][4];
     const int b = first + blockIdx.x;
     const BlockDesc D = desc[b];
     MeshParams &P = mp[D.mesh];
     const double inv_dx = P.inv_dx1 * double(1 << (D.level - 1));
+    const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
     unsigned long long m = 0, mc = 0;
     bool ok = true;
-    for (int c = threadIdx.x; c < CELLS; c += blockDim.x) {
+    for (int k = 0; k < BN; ++k) {
         double u[9];
-        for (int v = 0; v < NV; ++v) u[v] = U[(size_t(b) * NV + v) * CELLS + c];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) u[v] = U[(size_t(b) * NV + v) * CELLS + k * 256 + threadIdx.x];
+        if (XE && ((x + 2) & 15) < 4) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) XE[xe_index(NV, b, k, x >> 3, v) + y * 2 + (x & 1)] = u[v];
+        }
         bool ok2;
         double s, cm = 0.0;
         if (NV == 9) s = mhd_signal(u, P.gamma, inv_dx, cm, ok2);
@@ -441,35 +442,27 @@ __global__ __launch_bounds__(256) void k_smax(const BlockDesc *desc, MeshParams 
     if (!ok) atomicOr(&P.flags, 1);
 }
 
-// Per-mesh reductions, one workgroup per mesh of `meshes` (cmax: MHD only):
-//   mode 0 (end of a step): smax (and cmax) = max over the mesh's blocks, t += dt;
-//   mode 1 (start of a CFL step): dt = cfl / smax, c_h = cmax;
-//   mode 2 (after an upload): smax (and cmax) = max over the mesh's blocks;
-//   mode 3 (start of a step with a given dt): c_h = cmax.
-__global__ __launch_bounds__(256) void k_mesh_reduce(MeshParams *mp, const int *meshes,
-                                                     const unsigned long long *smax,
-                                                     const unsigned long long *cmax, int mode) {
-    __shared__ unsigned long long sMax[2][4];
+// Per-mesh reductions, one workgroup per mesh of `meshes` (cmax: MHD only), at
+// the end of a step (end = 1: t += dt, last_dt = dt) and after an upload: smax
+// (and cmax) = max over the mesh's blocks, and the dt of the next step, dt =
+// cfl / smax.  A step starts with no launch of its own: every kernel of it
+// reads dt, and c_h = cmax (the launch that set dt cost 2.7 us and its gap,
+// an 8-block step 30 -> 26 us).  Bound by latency, so the lanes follow the mesh
+// sizes: 4096 blocks take 7.2 us with 256 lanes and 5.4 with 1024, 8 blocks 2.7
+// and 3.6.
+__device__ __forceinline__ unsigned long long mesh_max(const unsigned long long *x, int n) {
+    unsigned long long m = 0;
+#pragma unroll 4
+    for (int q = threadIdx.x; q < n; q += int(blockDim.x)) m = x[q] > m ? x[q] : m;
+    return wave_max_u64(m);
+}
+__global__ __launch_bounds__(1024) void k_mesh_reduce(MeshParams *mp, const int *meshes,
+                                                      const unsigned long long *smax,
+                                                      const unsigned long long *cmax, int end) {
+    __shared__ unsigned long long sMax[2][16];
     MeshParams &P = mp[meshes[blockIdx.x]];
-    if (mode == 1 || mode == 3) {
-        if (threadIdx.x == 0) {
-            if (mode == 1) P.dt = P.cfl / __longlong_as_double(P.smax);
-            P.ch = __longlong_as_double(P.cmax);
-        }
-        return;
-    }
     const int first = P.first_block, n = P.nblocks;
-    unsigned long long m = 0, mc = 0;
-    for (int q = threadIdx.x; q < n; q += blockDim.x) {
-        const unsigned long long v = smax[first + q];
-        m = v > m ? v : m;
-        if (cmax) {
-            const unsigned long long w = cmax[first + q];
-            mc = w > mc ? w : mc;
-        }
-    }
-    m = wave_max_u64(m);
-    mc = wave_max_u64(mc);
+    const unsigned long long m = mesh_max(smax + first, n), mc = cmax ? mesh_max(cmax + first, n) : 0;
     if ((threadIdx.x & 63) == 0) {
         sMax[0][threadIdx.x >> 6] = m;
         sMax[1][threadIdx.x >> 6] = mc;
@@ -477,13 +470,18 @@ __global__ __launch_bounds__(256) void k_mesh_reduce(MeshParams *mp, const int *
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long r = sMax[0][0], rc = sMax[1][0];
-        for (int w = 1; w < 4; ++w) {
+        for (int w = 1; w < int(blockDim.x >> 6); ++w) {
             r = sMax[0][w] > r ? sMax[0][w] : r;
             rc = sMax[1][w] > rc ? sMax[1][w] : rc;
         }
+        if (end) {
+            const double dt = P.dt;
+            P.t = P.t + dt;
+            P.last_dt = dt;
+        }
         P.smax = r;
         P.cmax = rc;
-        if (mode == 0) P.t = P.t + P.dt;
+        P.dt = P.cfl / __longlong_as_double(r);
     }
 }
 
@@ -629,23 +627,19 @@ hipError_t launch_reflux_restrict(const RefluxTask *rt, int nref, const Restrict
     return hipGetLastError();
 }
 
-hipError_t launch_xexport(const double *U, double *XE, int first, int n, int NV, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_xexport, dim3(n), dim3(256), 0, s, U, XE, first, NV);
-    return hipGetLastError();
-}
-
-hipError_t launch_smax(const BlockDesc *desc, MeshParams *mp, const double *U, unsigned long long *smax,
+hipError_t launch_smax(const BlockDesc *desc, MeshParams *mp, const double *U, double *XE, unsigned long long *smax,
                        unsigned long long *cmax, int first, int n, int NV, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_smax, dim3(n), dim3(256), 0, s, desc, mp, U, smax, cmax, first, NV);
+    if (NV == 9) hipLaunchKernelGGL(k_smax<9>, dim3(n), dim3(256), 0, s, desc, mp, U, XE, smax, cmax, first);
+    else hipLaunchKernelGGL(k_smax<5>, dim3(n), dim3(256), 0, s, desc, mp, U, XE, smax, cmax, first);
     return hipGetLastError();
 }
 
+// nmax: blocks of the largest of the meshes
 hipError_t launch_mesh_reduce(MeshParams *mp, const int *meshes, int nmesh, const unsigned long long *smax,
-                              const unsigned long long *cmax, int mode, hipStream_t s) {
+                              const unsigned long long *cmax, int nmax, int end, hipStream_t s) {
     if (nmesh <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mesh_reduce, dim3(nmesh), dim3(256), 0, s, mp, meshes, smax, cmax, mode);
+    hipLaunchKernelGGL(k_mesh_reduce, dim3(nmesh), dim3(nmax > 512 ? 1024 : 256), 0, s, mp, meshes, smax, cmax, end);
     return hipGetLastError();
 }
 

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256, 2) void k_mhd_stage(SweepArgs a) {
     const double gamma = mp.gamma, gm1 = gamma - 1.0;
     const double inv_dx = mp.inv_dx1 * double(1 << (D.level - 1));
     const double dtdx = mp.dt * inv_dx;
-    const double ch = mp.ch;
+    const double ch = __longlong_as_double(mp.cmax);
     // the last stage also applies the second half of the GLM decay of psi
     // (the factor of k_glm_decay for h = dt/2, the same expression) to every
     // cell that no flux correction follows; k_reflux applies it to the
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256) void k_glm_decay(const BlockDesc *desc, MeshPa
     const MeshParams &P = mp[D.mesh];
     const double inv_dx = P.inv_dx1 * double(1 << (D.level - 1));
     const double h = hfrac * P.dt;
-    const double f = exp(-h * P.ch * P.glm_alpha * inv_dx);
+    const double f = exp(-h * __longlong_as_double(P.cmax) * P.glm_alpha * inv_dx);
     v2d *psi = reinterpret_cast<v2d *>(U + (size_t(b) * NV + 8) * CELLS);
 #pragma unroll
     for (int r = 0; r < CELLS / 512; ++r) {
