@@ -655,6 +655,7 @@ int Engine::enqueue_step(std::string &err) {
     // ghosts unless the set of meshes changed; MHD fills after the psi decay
     if (mhd || !ghosts_valid_)
         if ((e = enqueue_fill(0, err))) return e;
+    ghosts_valid_ = false;
     if ((e = enqueue_stage(1, 0, 1, 1.0, true, err))) return e;
     if (cfg_.rk == 3) {
         if ((e = enqueue_stage(3, 1, 2, 0.25, true, err))) return e;
@@ -706,6 +707,7 @@ int Engine::step_cfl(int nsteps, std::string &err) {
                 CHK(hipGraphInstantiate(&graph_exec_, graph_, nullptr, nullptr, 0));
             }
             CHK(hipGraphLaunch(graph_exec_, st));
+            ghosts_valid_ = nvar_ != 9;
         } else {
             if ((e = enqueue_step(err))) return e;
         }
@@ -733,8 +735,9 @@ int Engine::step_dt(int s, double dt, std::string &err) {
 int Engine::fill_ghosts(std::string &err) {
     int e = rebuild(err);
     if (e) return e;
+    if (ghosts_valid_) return AGILE_OK;   // filled by the last step, or since
     if ((e = enqueue_fill(0, err))) return e;
-    ghosts_valid_ = nvar_ != 9;
+    ghosts_valid_ = true;
     return AGILE_OK;
 }
 
@@ -810,13 +813,18 @@ int Engine::remap(int s, const std::vector<RegridSource> &src, double *out_dev, 
     int e = fill_ghosts(err);
     if (e) return e;
     const hipStream_t st = cfg_.stream;
+    // XE[1] is free between steps; the mesh's range there, 8 NV KB per block,
+    // holds the tasks of the at most 8 new leaves of every block
     RemapTask *d_t = d_tasks;
-    if (!d_t) CHK(hipMalloc(&d_t, std::max<size_t>(1, t.size()) * sizeof(RemapTask)));
+    if (!d_t) d_t = reinterpret_cast<RemapTask *>(XE_[1] + size_t(S.first) * nvar_ * XE_CELLS);
+    if (t.size() * sizeof(RemapTask) > size_t(n) * nvar_ * XE_CELLS * sizeof(double)) {
+        err = "remap: more than 8 new blocks per block";
+        return AGILE_EINVAL;
+    }
     hipError_t he = hipMemcpyAsync(d_t, t.data(), t.size() * sizeof(RemapTask), hipMemcpyHostToDevice, st);
     if (he == hipSuccess)
         he = launch_remap(d_t, int(t.size()), desc_, mp_, U_[0], halo_, nvar_, cfg_.physics == AGILE_SRHD, out_dev, st);
     if (he == hipSuccess) he = hipStreamSynchronize(st);
-    if (!d_tasks) (void)hipFree(d_t);
     if (he != hipSuccess) {
         err = std::string("remap: ") + hipGetErrorString(he);
         return AGILE_EDEVICE;

@@ -246,7 +246,7 @@ private:
     RefluxTask *d_reflux_ = nullptr;
     int nlist_ = 0, nmeshes_ = 0, nblocks_max_ = 0, nrestrict_ = 0, nreflux_ = 0;
     bool rr_indep_ = false;   // flux correction and restriction touch different blocks
-    bool ghosts_valid_ = false;   // halo slabs hold the ghost fill of U[0] (Euler)
+    bool ghosts_valid_ = false;   // halo slabs hold the ghost fill of U[0]
     std::vector<int> pro_off_, pro_cnt_;
     std::vector<char> pro_dep_;   // [level] waits for the level below (some mesh)
     bool dirty_ = true;

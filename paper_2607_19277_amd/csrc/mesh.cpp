@@ -16,15 +16,12 @@
 
 #include <algorithm>
 #include <cstring>
-#include <unordered_map>
+
+#include "block_table.hpp"
 
 namespace agile {
 
 namespace {
-
-inline uint64_t key_of(int level, int64_t x, int64_t y, int64_t z) {
-    return (uint64_t(level) << 60) | (uint64_t(x) << 40) | (uint64_t(y) << 20) | uint64_t(z);
-}
 
 inline uint64_t spread3(uint64_t v) {
     // spread the low 21 bits of v to every third bit
@@ -41,10 +38,8 @@ inline uint64_t morton(int64_t x, int64_t y, int64_t z) {
     return spread3(uint64_t(x)) | (spread3(uint64_t(y)) << 1) | (spread3(uint64_t(z)) << 2);
 }
 
-inline int64_t wrap(int64_t c, int64_t n) {
-    int64_t r = c % n;
-    return r < 0 ? r + n : r;
-}
+// periodic neighbour index: c in [-1, n]
+inline int64_t wrap(int64_t c, int64_t n) { return c < 0 ? c + n : (c >= n ? c - n : c); }
 
 // lower / upper tangential axes of a face normal to d
 inline int tan_a(int d) { return d == 0 ? 1 : 0; }
@@ -68,16 +63,17 @@ int build_plan(const PlanInput &in, int64_t n, const agile_block_desc *blocks, P
     for (int d = 0; d < 3; ++d)
         if (nbl[L][d] >= (int64_t(1) << 20)) return fail("too many blocks per axis on the finest level");
 
-    std::unordered_map<uint64_t, int> where;
-    where.reserve(size_t(n) * 2);
+    BlockTable where{size_t(n)};
+    unsigned present = 0;   // levels that hold blocks
     for (int64_t q = 0; q < n; ++q) {
         const agile_block_desc &b = blocks[q];
         if (b.level < 1 || b.level > L) return fail("block " + std::to_string(q) + ": level out of range");
         for (int d = 0; d < 3; ++d)
             if (b.idx[d] < 0 || b.idx[d] >= nbl[b.level][d])
                 return fail("block " + std::to_string(q) + ": index out of range");
-        uint64_t k = key_of(b.level, b.idx[0], b.idx[1], b.idx[2]);
-        if (!where.emplace(k, int(q)).second) return fail("block " + std::to_string(q) + ": duplicate");
+        if (!where.insert(block_key(b.level, b.idx[0], b.idx[1], b.idx[2]), int(q)))
+            return fail("block " + std::to_string(q) + ": duplicate");
+        present |= 1u << b.level;
     }
     // overlap (a leaf inside another leaf) and tiling by volume
     unsigned __int128 vol = 0, dom = (unsigned __int128)in.base[0] * in.base[1] * in.base[2];
@@ -86,7 +82,7 @@ int build_plan(const PlanInput &in, int64_t n, const agile_block_desc *blocks, P
         const agile_block_desc &b = blocks[q];
         for (int l = b.level - 1; l >= 1; --l) {
             int s = b.level - l;
-            if (where.count(key_of(l, b.idx[0] >> s, b.idx[1] >> s, b.idx[2] >> s)))
+            if ((present >> l & 1) && where.find(block_key(l, b.idx[0] >> s, b.idx[1] >> s, b.idx[2] >> s)) >= 0)
                 return fail("block " + std::to_string(q) + ": overlaps a coarser block");
         }
         vol += (unsigned __int128)1 << (3 * (L - b.level));
@@ -95,27 +91,27 @@ int build_plan(const PlanInput &in, int64_t n, const agile_block_desc *blocks, P
 
     // device order: level, then Morton code
     P.n = n;
+    std::vector<std::pair<uint64_t, int>> mk(static_cast<size_t>(n));   // the keys are distinct
+    for (int64_t q = 0; q < n; ++q) {
+        const agile_block_desc &b = blocks[q];
+        mk[q] = {(uint64_t(b.level) << 60) | morton(b.idx[0], b.idx[1], b.idx[2]), int(q)};
+    }
+    std::sort(mk.begin(), mk.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
     P.order.resize(n);
-    for (int64_t q = 0; q < n; ++q) P.order[q] = int(q);
-    std::vector<uint64_t> mk(n);
-    for (int64_t q = 0; q < n; ++q) mk[q] = morton(blocks[q].idx[0], blocks[q].idx[1], blocks[q].idx[2]);
-    std::stable_sort(P.order.begin(), P.order.end(), [&](int a, int b) {
-        if (blocks[a].level != blocks[b].level) return blocks[a].level < blocks[b].level;
-        return mk[a] < mk[b];
-    });
     P.perm.resize(n);
-    for (int64_t q = 0; q < n; ++q) P.perm[P.order[q]] = int(q);
+    for (int64_t q = 0; q < n; ++q) {
+        P.order[q] = mk[q].second;
+        P.perm[P.order[q]] = int(q);
+    }
     auto dev_of = [&](int level, int64_t x, int64_t y, int64_t z) -> int {
-        auto it = where.find(key_of(level, x, y, z));
-        return it == where.end() ? -1 : P.perm[it->second];
+        if (!(present >> level & 1)) return -1;
+        const int q = where.find(block_key(level, x, y, z));
+        return q < 0 ? -1 : P.perm[q];
     };
 
     P.desc.assign(n, BlockDesc{});
     P.prolong.assign(L + 1, {});
     P.levels = 0;
-    // fine flux register slot of (fine block, face) -> slot, filled while
-    // scanning the fine side; used by the coarse side afterwards
-    std::unordered_map<uint64_t, int> fine_reg;
     for (int64_t db = 0; db < n; ++db) {
         const agile_block_desc &b = blocks[P.order[db]];
         BlockDesc &D = P.desc[db];
@@ -147,7 +143,6 @@ int build_plan(const PlanInput &in, int64_t n, const agile_block_desc *blocks, P
                     D.nb[f] = -(t.slot + 1);
                     P.prolong[b.level].push_back(t);
                     D.freg[f] = P.nfreg++;
-                    fine_reg[uint64_t(db) * 8 + f] = D.freg[f];
                     continue;
                 }
             }
@@ -204,9 +199,11 @@ int build_plan(const PlanInput &in, int64_t n, const agile_block_desc *blocks, P
         r.face[r.nface] = f;
         r.cslot[r.nface] = P.desc[t.block].freg[f];
         for (int q = 0; q < 4; ++q) {
-            auto it = fine_reg.find(uint64_t(t.fine[q]) * 8 + (f ^ 1));
-            if (it == fine_reg.end()) return fail("internal: missing fine flux register");
-            r.fslot[r.nface][q] = it->second;
+            // the register of the fine side, whose ghost slab there is prolonged
+            const BlockDesc &F = P.desc[t.fine[q]];
+            const int ff = f ^ 1;
+            if (F.nb[ff] >= 0 || (F.cf_coarse >> ff & 1)) return fail("internal: missing fine flux register");
+            r.fslot[r.nface][q] = F.freg[ff];
         }
         r.nface++;
     }
