@@ -87,17 +87,16 @@ __device__ __forceinline__ void restrict_cell(const RestrictTask *__restrict__ t
     const int bx = d == 0 ? bn : ba;
     const int by = d == 1 ? bn : (d == 0 ? ba : bb);
     const int bz = d == 2 ? bn : bb;
-    const double *u = U + size_t(F) * NV * CELLS + (bz * 16 + by) * 16 + bx;
-    double ch[NV][8];
+    const double2v *u = reinterpret_cast<const double2v *>(U + size_t(F) * NV * CELLS + (bz * 16 + by) * 16 + bx);
+    double2v ch[NV][4];   // pairs along x (bx is even)
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            ch[v][k] = u[v * CELLS + ((k >> 2) * 16 + ((k >> 1) & 1)) * 16 + (k & 1)];
+        for (int k = 0; k < 4; ++k) ch[v][k] = u[v * (CELLS / 2) + (k >> 1) * 128 + (k & 1) * 8];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const double s = ((ch[v][0] + ch[v][1]) + (ch[v][2] + ch[v][3])) +
-                         ((ch[v][4] + ch[v][5]) + (ch[v][6] + ch[v][7]));
+        const double s = ((ch[v][0].x + ch[v][0].y) + (ch[v][1].x + ch[v][1].y)) +
+                         ((ch[v][2].x + ch[v][2].y) + (ch[v][3].x + ch[v][3].y));
         halo[(size_t(t->slot) * NV + v) * SLAB + c] = s * 0.125;
     }
 }
@@ -297,16 +296,17 @@ __device__ __forceinline__ void reflux_block(const RefluxTask *__restrict__ t, M
         const int cz = d == 2 ? xd : tb;
         const size_t cell = (size_t(cz) * 16 + cy) * 16 + cx;
         // every load of the face before its stores
-        double f4[NV][4], fc[NV], uo[NV];
+        const bool inx = XE && d == 0;   // the cells of an x face: from their copy, in whole runs
+        double2v f4[NV][2];              // fa is even
+        double fc[NV], uo[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const double *fp = fr + v * REG;
-            f4[v][0] = fp[fb * 16 + fa];
-            f4[v][1] = fp[fb * 16 + fa + 1];
-            f4[v][2] = fp[(fb + 1) * 16 + fa];
-            f4[v][3] = fp[(fb + 1) * 16 + fa + 1];
+            const double2v *fp = reinterpret_cast<const double2v *>(fr + v * REG + fb * 16 + fa);
+            f4[v][0] = fp[0];
+            f4[v][1] = fp[8];
             fc[v] = cr[v * REG + c];
-            uo[v] = U[(size_t(block) * NV + v) * CELLS + cell];
+            uo[v] = inx ? XE[xe_index(NV, block, cz, side, v) + cy * 2 + side]
+                        : U[(size_t(block) * NV + v) * CELLS + cell];
         }
         // final unless a later face of the list also holds the cell
         bool fin = true;
@@ -318,7 +318,7 @@ __device__ __forceinline__ void reflux_block(const RefluxTask *__restrict__ t, M
         double nu[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const double fm = ((f4[v][0] + f4[v][1]) + (f4[v][2] + f4[v][3])) * 0.25;
+            const double fm = ((f4[v][0].x + f4[v][0].y) + (f4[v][1].x + f4[v][1].y)) * 0.25;
             const double diff = fc[v] - fm;
             nu[v] = side ? uo[v] + w * diff : uo[v] - w * diff;
             // MHD, last stage: the second half of the GLM decay of psi, which
@@ -496,7 +496,6 @@ __global__ void k_set_dt(MeshParams *mp, int mesh, double dt) {
 // streaming.  Bound by HBM on large meshes (4096 blocks 247 -> 230 us, 5.8
 // TB/s) and by latency on small ones, where a workgroup per block left most of
 // the chip idle (64 blocks 33 -> 7.6 us).
-typedef double v2d __attribute__((ext_vector_type(2)));
 template <typename W>
 __global__ __launch_bounds__(256) void k_permute(const W *__restrict__ src, W *__restrict__ dst, const int *map,
                                                  int first, int per_block, int parts, int gather) {
@@ -518,7 +517,7 @@ __global__ __launch_bounds__(256) void k_permute(const W *__restrict__ src, W *_
 // sustains on a plain read + write stream: one word per lane and pass,
 // nontemporal loads and stores (the fastest of the shapes measured on gfx950:
 // 4, 8 words in flight per lane and smaller grids were slower).
-__global__ __launch_bounds__(256) void k_stream_copy(const v2d *__restrict__ src, v2d *__restrict__ dst, size_t n) {
+__global__ __launch_bounds__(256) void k_stream_copy(const double2v *__restrict__ src, double2v *__restrict__ dst, size_t n) {
     const size_t stride = size_t(gridDim.x) * 256;
     for (size_t i = size_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += stride)
         __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
@@ -529,8 +528,8 @@ hipError_t launch_stream_copy(const void *src, void *dst, size_t bytes, hipStrea
     if (n == 0) return hipSuccess;
     const size_t want = (n + 255) / 256;
     const unsigned grid = unsigned(want < (size_t(1) << 22) ? want : (size_t(1) << 22));
-    hipLaunchKernelGGL(k_stream_copy, dim3(grid), dim3(256), 0, s, static_cast<const v2d *>(src),
-                       static_cast<v2d *>(dst), n);
+    hipLaunchKernelGGL(k_stream_copy, dim3(grid), dim3(256), 0, s, static_cast<const double2v *>(src),
+                       static_cast<double2v *>(dst), n);
     return hipGetLastError();
 }
 
@@ -658,8 +657,8 @@ hipError_t launch_permute(const double *src, double *dst, const int *map, int fi
     if (nblocks <= 0) return hipSuccess;
     if (per_block % 2 == 0 && aligned16(src, dst)) {
         const int parts = (per_block / 2 + 1023) / 1024;
-        hipLaunchKernelGGL(k_permute<v2d>, dim3(unsigned(nblocks) * parts), dim3(256), 0, s,
-                           reinterpret_cast<const v2d *>(src), reinterpret_cast<v2d *>(dst), map, first,
+        hipLaunchKernelGGL(k_permute<double2v>, dim3(unsigned(nblocks) * parts), dim3(256), 0, s,
+                           reinterpret_cast<const double2v *>(src), reinterpret_cast<double2v *>(dst), map, first,
                            per_block / 2, parts, gather);
     } else {
         const int parts = (per_block + 1023) / 1024;
@@ -673,8 +672,8 @@ hipError_t launch_permute_tiles(const double *src, double *dst, const int *map, 
                                 int te, int gather, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
     if (aligned16(src, dst))
-        hipLaunchKernelGGL(k_permute_tiles<v2d>, dim3(unsigned(ntiles) * NV * 2), dim3(256), 0, s,
-                           reinterpret_cast<const v2d *>(src), reinterpret_cast<v2d *>(dst), map, first, NV, te, gather);
+        hipLaunchKernelGGL(k_permute_tiles<double2v>, dim3(unsigned(ntiles) * NV * 2), dim3(256), 0, s,
+                           reinterpret_cast<const double2v *>(src), reinterpret_cast<double2v *>(dst), map, first, NV, te, gather);
     else
         hipLaunchKernelGGL(k_permute_tiles<double>, dim3(unsigned(ntiles) * NV * 4), dim3(256), 0, s, src, dst, map,
                            first, NV, te, gather);
@@ -698,17 +697,19 @@ hipError_t launch_read_ghosts(const BlockDesc *desc, const double *U, const doub
 // sums in x, y, z order, no contraction and IEEE division and square root
 // (E = 0 where v is zero on the whole stencil and both sums vanish),
 // so the block maximum is the same number on any machine.  One workgroup per
-// block, lane = column; out[block - first] = max over the block's cells.
+// block, lane = column and every fourth plane (bound by the latency of the
+// stencil's loads: 59 us on 512 to 2304 blocks with a lane per column, now
+// 34); out[block - first] = max over the block's cells.
 template <int NV>
-__global__ __launch_bounds__(256) void k_lohner(const BlockDesc *__restrict__ desc, const double *__restrict__ U,
+__global__ __launch_bounds__(1024) void k_lohner(const BlockDesc *__restrict__ desc, const double *__restrict__ U,
                                                 const double *__restrict__ halo, int first, int v, double eps,
                                                 double *__restrict__ out) {
 #pragma clang fp contract(off)
-    __shared__ unsigned long long sMax[4];
+    __shared__ unsigned long long sMax[16];
     const int b = first + blockIdx.x;
-    const int i = threadIdx.x & 15, j = threadIdx.x >> 4;
+    const int i = threadIdx.x & 15, j = (threadIdx.x >> 4) & 15;
     unsigned long long m = 0;
-    for (int k = 0; k < BN; ++k) {
+    for (int k = threadIdx.x >> 8; k < BN; k += 4) {
         const double u0 = U[(size_t(b) * NV + v) * CELLS + (k * 16 + j) * 16 + i];
         double num = 0.0, den = 0.0;
 #pragma unroll
@@ -730,72 +731,99 @@ __global__ __launch_bounds__(256) void k_lohner(const BlockDesc *__restrict__ de
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long r = sMax[0];
-        for (int w = 1; w < 4; ++w) r = sMax[w] > r ? sMax[w] : r;
+        for (int w = 1; w < 16; ++w) r = sMax[w] > r ? sMax[w] : r;
         out[blockIdx.x] = __longlong_as_double(r);
     }
 }
 
-// Data of the new leaves of a regrid, one workgroup per new leaf, lane =
-// column: kind 0 copies block src[0]; kind 1 is child `octant` of parent
-// src[0] -- parent cell plus, in x, y, z order, +/- 1/4 minmod of the
-// parent's axis differences (the parent's face ghosts at its sides), as the
-// ghost prolongation; kind 2 is the mean of the 8 children src[octant],
-// summed pairwise as the restriction.  All indices are pool indices of the
-// old mesh, whose ghosts must be filled.  SRHD (srhd != 0) prolongs the
-// primitives, as its ghost prolongation: one lane per child cell.
+// Data of the new leaves of a regrid, one workgroup per new leaf and variable:
+// kind 0 copies block src[0]; kind 1 is child `octant` of parent src[0] --
+// parent cell plus, in x, y, z order, +/- 1/4 minmod of the parent's axis
+// differences (the parent's face ghosts at its sides), as the ghost
+// prolongation; kind 2 is the mean of the 8 children src[octant], summed
+// pairwise as the restriction.  All indices are pool indices of the old mesh,
+// whose ghosts must be filled.  SRHD (srhd != 0) prolongs the primitives, as
+// its ghost prolongation: one lane per child cell, the cells shared out over
+// the leaf's workgroups.  Bound by HBM: rows are read and written in 16-byte
+// words, and a lane of kind 1 forms a parent's slopes once for its 8 children
+// (512 -> 2304 and 2304 -> 512 blocks 244 us on average with a workgroup per
+// leaf, a cell per lane; now 100).
 template <int NV>
 __global__ __launch_bounds__(256) void k_remap(const RemapTask *__restrict__ tasks, const BlockDesc *__restrict__ desc,
                                                const MeshParams *__restrict__ mp, const double *__restrict__ U,
                                                const double *__restrict__ halo, double *__restrict__ out, int srhd) {
-    const RemapTask *t = tasks + blockIdx.x;   // read through the pointer (no scratch copy)
+    const int leaf = blockIdx.x / NV, v = blockIdx.x - leaf * NV;
+    const RemapTask *t = tasks + leaf;   // read through the pointer (no scratch copy)
     const int kind = t->kind, oc = t->octant;
-    double *o = out + size_t(blockIdx.x) * NV * CELLS;
+    double *o = out + (size_t(leaf) * NV + v) * CELLS;
+    double2v *o2 = reinterpret_cast<double2v *>(o);
     if (kind == 0) {
-        const double *src = U + size_t(t->src[0]) * NV * CELLS;
-#pragma unroll 4
-        for (int e = threadIdx.x; e < NV * CELLS; e += 256) o[e] = src[e];
+        const double2v *src = reinterpret_cast<const double2v *>(U + (size_t(t->src[0]) * NV + v) * CELLS);
+        double2v x[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) x[r] = src[256 * r + threadIdx.x];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) o2[256 * r + threadIdx.x] = x[r];
         return;
     }
-    if (NV == 5 && srhd && kind == 1) {
-        const int P = t->src[0];
+    if (kind == 2) {
+        // two cells along x per lane and trip
+#pragma unroll 2
+        for (int e = threadIdx.x; e < CELLS / 2; e += 256) {
+            const int i = 2 * (e & 7), j = (e >> 3) & 15, k = e >> 7;
+            const int F = t->src[(i >> 3) + 2 * (j >> 3) + 4 * (k >> 3)];
+            const double2v *u = reinterpret_cast<const double2v *>(U + (size_t(F) * NV + v) * CELLS +
+                                                         ((2 * (k & 7)) * 16 + 2 * (j & 7)) * 16 + 2 * (i & 7));
+            double2v r;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const double2v a = u[c], b = u[8 + c], d = u[128 + c], f = u[136 + c];
+                const double s = ((a.x + a.y) + (b.x + b.y)) + ((d.x + d.y) + (f.x + f.y));
+                r[c] = s * 0.125;
+            }
+            o2[e] = r;
+        }
+        return;
+    }
+    const int P = t->src[0];
+    const int px = (oc & 1) * 8, py = ((oc >> 1) & 1) * 8, pz = (oc >> 2) * 8;
+    if (NV == 5 && srhd) {
         const double g = mp[desc[P].mesh].gamma;
 #pragma unroll 1
-        for (int cell = threadIdx.x; cell < CELLS; cell += 256) {
+        for (int cell = v * 256 + threadIdx.x; cell < CELLS; cell += NV * 256) {
             const int i = cell & 15, j = (cell >> 4) & 15, k = cell >> 8;
             double wc[5], q[3][5], c[5];
-            const bool ok = srhd_parent(desc, U, halo, P, (oc & 1) * 8 + (i >> 1), ((oc >> 1) & 1) * 8 + (j >> 1),
-                                        (oc >> 2) * 8 + (k >> 1), g, wc, q);
+            const bool ok = srhd_parent(desc, U, halo, P, px + (i >> 1), py + (j >> 1), pz + (k >> 1), g, wc, q);
             srhd_child(wc, q, i & 1, j & 1, k & 1, g, ok, c);
 #pragma unroll
-            for (int v = 0; v < 5; ++v) o[v * CELLS + cell] = c[v];
+            for (int w = 0; w < 5; ++w) out[(size_t(leaf) * NV + w) * CELLS + cell] = c[w];
         }
         return;
     }
-#pragma unroll 1
-    for (int e = threadIdx.x; e < NV * CELLS; e += 256) {
-        const int v = e >> 12, cell = e & (CELLS - 1);
-        const int i = cell & 15, j = (cell >> 4) & 15, k = cell >> 8;
-        double val;
-        if (kind == 2) {
-            const int F = t->src[(i >> 3) + 2 * (j >> 3) + 4 * (k >> 3)];
-            const double *u = U + (size_t(F) * NV + v) * CELLS + ((2 * (k & 7)) * 16 + 2 * (j & 7)) * 16 + 2 * (i & 7);
-            const double s = ((u[0] + u[1]) + (u[16] + u[17])) + ((u[256] + u[257]) + (u[272] + u[273]));
-            val = s * 0.125;
-        } else {
-            const int P = t->src[0];
-            const int cx = (oc & 1) * 8 + (i >> 1), cy = ((oc >> 1) & 1) * 8 + (j >> 1), cz = (oc >> 2) * 8 + (k >> 1);
-            const double vc = U[(size_t(P) * NV + v) * CELLS + (cz * 16 + cy) * 16 + cx];
-            val = vc;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const double vm = block_value(desc, U, halo, NV, P, v, cx - (d == 0), cy - (d == 1), cz - (d == 2));
-                const double vp = block_value(desc, U, halo, NV, P, v, cx + (d == 0), cy + (d == 1), cz + (d == 2));
-                const double q = 0.25 * minmod(vc - vm, vp - vc);
-                const int odd = d == 0 ? (i & 1) : (d == 1 ? (j & 1) : (k & 1));
-                val = odd ? val + q : val - q;
-            }
+    for (int half = 0; half < 2; ++half) {
+        const int i = threadIdx.x & 7, j = (threadIdx.x >> 3) & 7, k = (threadIdx.x >> 6) + 4 * half;
+        const int cx = px + i, cy = py + j, cz = pz + k;
+        const double vc = U[(size_t(P) * NV + v) * CELLS + (cz * 16 + cy) * 16 + cx];
+        double q[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const double vm = block_value(desc, U, halo, NV, P, v, cx - (d == 0), cy - (d == 1), cz - (d == 2));
+            const double vp = block_value(desc, U, halo, NV, P, v, cx + (d == 0), cy + (d == 1), cz + (d == 2));
+            q[d] = 0.25 * minmod(vc - vm, vp - vc);
         }
-        o[e] = val;
+        const double x[2] = {vc - q[0], vc + q[0]};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int sy = c & 1, sz = c >> 1;
+            double2v r;
+#pragma unroll
+            for (int sx = 0; sx < 2; ++sx) {
+                const double y = sy ? x[sx] + q[1] : x[sx] - q[1];
+                r[sx] = sz ? y + q[2] : y - q[2];
+            }
+            o2[((2 * k + sz) * 16 + 2 * j + sy) * 8 + i] = r;
+        }
     }
 }
 
@@ -803,8 +831,8 @@ hipError_t launch_lohner(const BlockDesc *desc, const double *U, const double *h
                          double eps, double *out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     if (v < 0 || v >= NV) return hipErrorInvalidValue;
-    if (NV == 9) hipLaunchKernelGGL(k_lohner<9>, dim3(n), dim3(256), 0, s, desc, U, halo, first, v, eps, out);
-    else hipLaunchKernelGGL(k_lohner<5>, dim3(n), dim3(256), 0, s, desc, U, halo, first, v, eps, out);
+    if (NV == 9) hipLaunchKernelGGL(k_lohner<9>, dim3(n), dim3(1024), 0, s, desc, U, halo, first, v, eps, out);
+    else hipLaunchKernelGGL(k_lohner<5>, dim3(n), dim3(1024), 0, s, desc, U, halo, first, v, eps, out);
     return hipGetLastError();
 }
 
@@ -812,8 +840,8 @@ hipError_t launch_remap(const RemapTask *t, int n, const BlockDesc *desc, const 
                         const double *halo, int NV, int srhd, double *out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     if (srhd && NV != 5) return hipErrorInvalidValue;
-    if (NV == 9) hipLaunchKernelGGL(k_remap<9>, dim3(n), dim3(256), 0, s, t, desc, mp, U, halo, out, 0);
-    else hipLaunchKernelGGL(k_remap<5>, dim3(n), dim3(256), 0, s, t, desc, mp, U, halo, out, srhd);
+    if (NV == 9) hipLaunchKernelGGL(k_remap<9>, dim3(unsigned(n) * 9), dim3(256), 0, s, t, desc, mp, U, halo, out, 0);
+    else hipLaunchKernelGGL(k_remap<5>, dim3(unsigned(n) * 5), dim3(256), 0, s, t, desc, mp, U, halo, out, srhd);
     return hipGetLastError();
 }
 
