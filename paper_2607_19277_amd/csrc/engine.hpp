@@ -189,17 +189,18 @@ public:
     // goes with the work items of the fullest of the 256 CUs times a work
     // item's length, k planes and about 1.4 planes' worth of prologue, plus a
     // part for ramp and tail: T(k) ~ ceil(blocks (16/k) / 256) (k + 1.4) + t(k),
-    // t = 8, 6.5, 5 planes for k = 16, 8, 4; the smallest T, the larger k on a
-    // tie.  Steps of uniform boxes (HLLC, us, k = 16 / 8 / 4): 64 blocks 84 / 54
+    // t = 8, 6.5, 5, 4.2, 3.4 planes for k = 16, 8, 4, 2, 1 (MHD: at least 2);
+    // the smallest T, the larger k on a tie.  Steps of uniform boxes (HLLC, us, k = 16 / 8 / 4): 64 blocks 84 / 54
     // / 40, 180: 86 / 74 / 70, 294: 120 / 105 / 99, 343: 119 / 108 / 114, 448:
     // 126 / 129 / 132, 576: 178 / 159 / 163, 810: 221 / 212 / 222, 1728: 402 /
-    // 415 / 455; FP32 flux, LF with van Leer and SRHD order alike.
+    // 415 / 455; FP32 flux, LF with van Leer and SRHD order alike.  k = 2 / 1
+    // (HLL): 4 blocks 25.4 / 22.9, 8: 26.7 / 24.7, 16: 28.0 / 26.1.
     int auto_kslab() const {
         int best = 16;
         double t = 0.0;
-        for (int k = 16; k >= 2; k /= 2) {
+        for (int k = 16; k >= (nvar_ == 9 ? 2 : 1); k /= 2) {
             const int items = (nlist_ * (BN / k) + 255) / 256;
-            const double c = items * (k + 1.4) + (k == 16 ? 8.0 : (k == 8 ? 6.5 : (k == 4 ? 5.0 : 4.2)));
+            const double c = items * (k + 1.4) + (k == 16 ? 8.0 : (k == 8 ? 6.5 : (k == 4 ? 5.0 : (k == 2 ? 4.2 : 3.4))));
             if (k == 16 || c < t - 1e-9) {
                 t = c;
                 best = k;

@@ -218,9 +218,9 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
     // stores of 64-byte pieces per wave; ten steps of 1856 blocks 5437 -> 5360
     // us, with FP32 fluxes 4977 -> 4885 us)
     const int xpos = (i < NG ? i : NV * BN * NG + i - (BN - NG)) + j * NG;
-    auto export_x = [&](int k) {
+    auto export_x = [&](int k, int buf) {
         if (tid < NV * BN * NG)
-            __builtin_nontemporal_store(reinterpret_cast<const double2v *>(sXE[k & 1])[tid],
+            __builtin_nontemporal_store(reinterpret_cast<const double2v *>(sXE[buf])[tid],
                                         reinterpret_cast<double2v *>(a.XEout + xe_index(NV, b, k, 0, 0)) + tid);
     };
 
@@ -251,8 +251,8 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
             wLz[v] = wk[v] + R(HALF<LIM>) * s0;
         }
         riemann<RS, R>(wL, wR, gammaR, igm1R, Flo);
-        put_own(k0 & 1, wk);
-        if (role < 2) put_ghost(k0 & 1, G0);
+        put_own(0, wk);
+        if (role < 2) put_ghost(0, G0);
     }
     if (k0 == 0 && D.freg[4] >= 0) keep(D.freg[4], colp, Flo[0], Flo[2], Flo[3], Flo[1], Flo[4]);
     __syncthreads();
@@ -265,8 +265,8 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
     // k+1 into LDS (the last plane writes one that is not used), barrier,
     // update of plane k.  The column's cell k+2 and the ghosts of plane k+1
     // are loaded at the top and first used after the x and y faces.
-    auto plane = [&](const int k) __attribute__((always_inline)) {
-        const int cur = k & 1, nxt = cur ^ 1;
+    auto plane = [&](const int k, const int cur) __attribute__((always_inline)) {
+        const int nxt = cur ^ 1;
         double C2[NV], G[NV], Un[NV];
         zload(k + 2, C2);
         if (role < 2) gload(min(k + 1, k1 - 1), G);
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
                 else out[v] = 0.5 * (Un[v] + u1);
                 __builtin_nontemporal_store(out[v], uniform_at(a.Uout + blk + v * CELLS, cell8));
             }
-            if (k > k0) export_x(k - 1);
+            if (k > k0) export_x(k - 1, nxt);
             if (i < 2 || i >= BN - 2) {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) sXE[cur][xpos + v * (BN * NG)] = out[v];
@@ -399,22 +399,22 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
         }
     };
     if (sizeof(R) == 8) {
-        // two planes per trip (slabs have an even number of planes, starting
-        // at an even plane): the register ring then needs about half the moves
+        // two planes per trip (slabs have one plane or an even number): the
+        // register ring then needs about half the moves
         for (int k = k0; k < k1; k += 2) {
-            __builtin_assume((k & 1) == 0);
-            plane(k);
+            plane(k, 0);
             __builtin_amdgcn_sched_barrier(0);
-            plane(k + 1);
+            if (k1 - k0 == 1) break;
+            plane(k + 1, 1);
         }
     } else {
         // FP32 runs three waves per SIMD; the longer body would not fit
-        for (int k = k0; k < k1; ++k) plane(k);
+        for (int k = k0; k < k1; ++k) plane(k, (k - k0) & 1);
     }
     // flux register of the +z face (Flo holds the flux of face 15+1/2)
     if (k1 == BN && D.freg[5] >= 0) keep(D.freg[5], colp, Flo[0], Flo[2], Flo[3], Flo[1], Flo[4]);
     __syncthreads();
-    export_x(k1 - 1);
+    export_x(k1 - 1, (k1 - 1 - k0) & 1);
     if (!ok) atomicOr(&mp.flags, 1);
     if (LAST) {
         unsigned long long *sMax = reinterpret_cast<unsigned long long *>(sP);   // no longer read
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
 
 hipError_t launch_stage(const StageArgs &a, int riemann, int precision, hipStream_t s) {
     if (a.nblocks <= 0) return hipSuccess;
-    if (a.kslab != 16 && a.kslab != 8 && a.kslab != 4 && a.kslab != 2) return hipErrorInvalidValue;
+    if (a.kslab != 16 && a.kslab != 8 && a.kslab != 4 && a.kslab != 2 && a.kslab != 1) return hipErrorInvalidValue;
     if (a.stage < 1 || a.stage > 4 || riemann < 0 || riemann > 3 || a.limiter < 0 || a.limiter > 1)
         return hipErrorInvalidValue;
     const dim3 grid(xcd_grid(a.nblocks * (BN / a.kslab), a.xcd)), block(256);

@@ -132,18 +132,18 @@ def test_srhd_step_in_every_regime(agile, flow, limiter):
 @pytest.mark.parametrize("precision", ["fp64", "fp32flux"])
 @pytest.mark.parametrize("physics", ["euler", "srhd", "mhd"])
 def test_cells_do_not_depend_on_the_number_of_blocks(agile, physics, precision):
-    """A periodic state of 2^3 blocks repeated to 4^3, 6^3 and 8^3 blocks: the
-    stage then takes 2, 4, 8 and 16 planes per work item, and every copy must
-    hold the same bits after the same step."""
+    """A periodic state of 2^3 blocks repeated to 4 x 4 x 2, 4^3, 6^3 and 8^3
+    blocks: the stage then takes 1 (MHD 2), 2, 4, 8 and 16 planes per work item,
+    and every copy must hold the same bits after the same step."""
     base = W.uniform_blocks((2, 2, 2))
     w = {"euler": W.smooth_random, "srhd": W.srhd_smooth_random, "mhd": W.mhd_smooth_random}[physics](base, (2, 2, 2), 1, 5)
     prec = agile.FP64 if precision == "fp64" else agile.FP32_FLUX
     of = {tuple(r[1:]): q for q, r in enumerate(base.tolist())}
     dt, first = Oracle(w).dt(), None
-    for n in (2, 4, 6, 8):
-        blocks = W.uniform_blocks((n, n, n))
+    for n in ((2, 2, 2), (4, 4, 2), (4, 4, 4), (6, 6, 6), (8, 8, 8)):
+        blocks = W.uniform_blocks(n)
         src = np.array([of[tuple(c % 2 for c in r[1:])] for r in blocks.tolist()])
-        m = agile.Mesh(w.physics, w.riemann, prec, w.gamma, w.cfl, w.glm_alpha, (n, n, n), hi=(n / 2,) * 3)
+        m = agile.Mesh(w.physics, w.riemann, prec, w.gamma, w.cfl, w.glm_alpha, n, hi=tuple(c / 2 for c in n))
         m.set_blocks(blocks, w.U[src])
         m.step(dt)
         U = m.readback()
