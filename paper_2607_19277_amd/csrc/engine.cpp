@@ -103,11 +103,17 @@ void blocks_from_tiles(const double *tiles, double *blocks, const int *perm, int
 
 Engine::~Engine() { free_all(); }
 
+void Engine::drop_graphs() {
+    for (StepGraph *G : {&graph_one_, &graph_many_}) {
+        if (G->exec) (void)hipGraphExecDestroy(G->exec);
+        if (G->graph) (void)hipGraphDestroy(G->graph);
+        *G = StepGraph{};
+    }
+    replays_ = 0;
+}
+
 void Engine::free_all() {
-    if (graph_exec_) (void)hipGraphExecDestroy(graph_exec_);
-    if (graph_) (void)hipGraphDestroy(graph_);
-    graph_exec_ = nullptr;
-    graph_ = nullptr;
+    drop_graphs();
     for (MeshSlot &s : slots_) s.d_perm = nullptr;
     void *ptrs[] = {U_[0], U_[1], U_[2], XE_[0], XE_[1], XE_[2], halo_, freg_, desc_, mp_, smax_,
                     d_list_, d_meshes_, d_restrict_, d_prolong_, d_reflux_, d_perm_};
@@ -475,10 +481,7 @@ int Engine::rebuild(std::string &err) {
         for (const RestrictTask &t : res)
             for (int q = 0; q < 4; ++q) rr_indep_ = rr_indep_ && !corrected[t.fine[q]];
     }
-    if (graph_exec_) (void)hipGraphExecDestroy(graph_exec_);
-    if (graph_) (void)hipGraphDestroy(graph_);
-    graph_exec_ = nullptr;
-    graph_ = nullptr;
+    drop_graphs();
     dirty_ = false;
     ghosts_valid_ = false;   // meshes were added, removed or (de)activated
     return AGILE_OK;
@@ -670,49 +673,62 @@ int Engine::enqueue_step(std::string &err) {
     return AGILE_OK;
 }
 
+// Capture `steps` steps into G.
+int Engine::capture_steps(int steps, StepGraph &G, std::string &err) {
+    const hipStream_t st = cfg_.stream;
+    struct Clock {
+        double &ms;
+        std::chrono::steady_clock::time_point t0;
+        ~Clock() { ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count(); }
+    } clock{build_ms, std::chrono::steady_clock::now()};
+    graph_builds++;
+    CHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
+    capturing_ = true;
+    std::string e2;
+    int rc = AGILE_OK;
+    for (int q = 0; q < steps && !rc; ++q) rc = enqueue_step(e2);
+    capturing_ = false;
+    hipGraph_t g = nullptr;
+    const hipError_t ec = hipStreamEndCapture(st, &g);
+    if (rc || ec != hipSuccess) {
+        if (g) (void)hipGraphDestroy(g);
+        err = rc ? e2 : std::string("graph capture: ") + hipGetErrorString(ec);
+        return rc ? rc : AGILE_EDEVICE;
+    }
+    G.graph = g;
+    CHK(hipGraphInstantiate(&G.exec, G.graph, nullptr, nullptr, 0));
+    return AGILE_OK;
+}
+
 int Engine::step_cfl(int nsteps, std::string &err) {
     int e = rebuild(err);
     if (e) return e;
     if (nlist_ == 0) return AGILE_OK;
     const hipStream_t st = cfg_.stream;
-    for (int q = 0; q < nsteps; ++q) {
+    for (int q = 0, done; q < nsteps; q += done) {
+        done = 1;
         if (use_graph && !timing_ && st != nullptr) {
             // the captured step assumes valid ghosts at its start (Euler)
             if (!ghosts_valid_ && nvar_ != 9) {
                 if ((e = enqueue_fill(0, err))) return e;
                 ghosts_valid_ = true;
             }
-            if (!graph_exec_) {
-                struct Clock {
-                    double &ms;
-                    std::chrono::steady_clock::time_point t0;
-                    ~Clock() {
-                        ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-                    }
-                } clock{build_ms, std::chrono::steady_clock::now()};
-                graph_builds++;
-                CHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-                capturing_ = true;
-                std::string e2;
-                const int rc = enqueue_step(e2);
-                capturing_ = false;
-                hipGraph_t g = nullptr;
-                const hipError_t ec = hipStreamEndCapture(st, &g);
-                if (rc || ec != hipSuccess) {
-                    if (g) (void)hipGraphDestroy(g);
-                    err = rc ? e2 : std::string("graph capture: ") + hipGetErrorString(ec);
-                    return rc ? rc : AGILE_EDEVICE;
-                }
-                graph_ = g;
-                CHK(hipGraphInstantiate(&graph_exec_, graph_, nullptr, nullptr, 0));
-            }
-            CHK(hipGraphLaunch(graph_exec_, st));
+            // Launching a graph leaves the GPU idle for about as long as one of
+            // its smallest kernels runs (a step of 8 blocks 24.7 us, in graphs of
+            // 8 steps 21.5; of 64 blocks 38.7 and 35.3).  Meshes that keep stepping get a graph of
+            // several steps; its capture pays off after some tens of steps, so
+            // it is not made for a set of meshes that soon changes.
+            if (replays_ >= 4 * GRAPH_STEPS && nsteps - q >= GRAPH_STEPS) done = GRAPH_STEPS;
+            StepGraph &G = done == 1 ? graph_one_ : graph_many_;
+            if (!G.exec && (e = capture_steps(done, G, err))) return e;
+            CHK(hipGraphLaunch(G.exec, st));
+            replays_ = std::min(replays_ + done, 4 * GRAPH_STEPS);
             ghosts_valid_ = nvar_ != 9;
         } else {
             if ((e = enqueue_step(err))) return e;
         }
         for (MeshSlot &S : slots_)
-            if (S.used && S.active) S.steps_done++;
+            if (S.used && S.active) S.steps_done += done;
         if (pairs_used_ > 4096 && (e = tcollect(err))) return e;
     }
     return AGILE_OK;

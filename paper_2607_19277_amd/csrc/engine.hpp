@@ -223,6 +223,13 @@ private:
     int enqueue_correct(int out, double bw, bool last, bool fill, std::string &err);
     int enqueue_stage(int kind, int in, int out, double bw, bool fill, std::string &err);
     int enqueue_step(std::string &err);
+    static constexpr int GRAPH_STEPS = 8;
+    struct StepGraph {
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+    };
+    int capture_steps(int steps, StepGraph &G, std::string &err);
+    void drop_graphs();
     int tbegin(int kind, std::string &err);
     int tend(int kind, std::string &err);
     int tcollect(std::string &err);
@@ -252,8 +259,8 @@ private:
     std::vector<char> pro_dep_;   // [level] waits for the level below (some mesh)
     bool dirty_ = true;
     // graph of one CFL step
-    hipGraph_t graph_ = nullptr;
-    hipGraphExec_t graph_exec_ = nullptr;
+    StepGraph graph_one_, graph_many_;   // one step, GRAPH_STEPS steps
+    int replays_ = 0;                    // steps replayed since the set of meshes changed, at most 4 GRAPH_STEPS
     bool capturing_ = false;
     // timing
     int timing_ = 0;              // bit mask of timed kernel classes
