@@ -369,8 +369,8 @@ int Engine::add(const agile_config &cfg, Plan &&P, const double *u, int u_on_dev
     std::vector<double> tmp;
     if (!e) {
         if (u_on_device) {
-            e = u_edge == 1 ? launch_permute(u, U_[0], S.d_perm, first, n, int(per), 0, st)
-                            : launch_permute_tiles(u, U_[0], S.d_perm, first, n, nvar_, u_edge, 0, st);
+            // a state in 16^3 blocks is copied by the scan below
+            if (u_edge != 1) e = launch_permute_tiles(u, U_[0], S.d_perm, first, n, nvar_, u_edge, 0, st);
         } else {
             tmp.resize(size_t(n) * per);
             if (u_edge == 1) {
@@ -383,7 +383,8 @@ int Engine::add(const agile_config &cfg, Plan &&P, const double *u, int u_on_dev
                                hipMemcpyHostToDevice, st);
         }
     }
-    e = e ? e : launch_smax(desc_, mp_, U_[0], XE_[0], smax_, cmax_, first, n, nvar_, st);
+    e = e ? e : launch_smax(desc_, mp_, U_[0], XE_[0], smax_, cmax_, first, n, nvar_,
+                            u_on_device && u_edge == 1 ? u : nullptr, S.d_perm, st);
     e = e ? e : launch_mesh_reduce(mp_, d_meshes_ + cfg_.cap_meshes + s, 1, smax_, cmax_, n, 0, st);
     e = e ? e : hipStreamSynchronize(st);
     if (e) {
@@ -769,7 +770,7 @@ int Engine::read_state(int s, double *out, int out_on_device, std::string &err) 
     const size_t per = size_t(nvar_) * CELLS;
     const hipStream_t st = cfg_.stream;
     if (out_on_device) {
-        if (S.tile_edge == 1) CHK(launch_permute(U_[0], out, S.d_perm, S.first, n, int(per), 1, st));
+        if (S.tile_edge == 1) CHK(launch_permute(U_[0], out, S.d_perm, S.first, n, int(per), st));
         else CHK(launch_permute_tiles(U_[0], out, S.d_perm, S.first, n, nvar_, S.tile_edge, 1, st));
         return AGILE_OK;
     }
@@ -859,7 +860,7 @@ int Engine::read_ghosts(int s, double *out, int out_on_device, std::string &err)
     double *scratch = U_[1] + size_t(S.first) * per;
     CHK(launch_read_ghosts(desc_, U_[0], halo_, scratch, S.first, n, nvar_, st));
     if (out_on_device) {
-        CHK(launch_permute(scratch, out, S.d_perm, 0, n, int(pg), 1, st));
+        CHK(launch_permute(scratch, out, S.d_perm, 0, n, int(pg), st));
         return AGILE_OK;
     }
     std::vector<double> tmp(size_t(n) * pg);
@@ -1056,7 +1057,7 @@ int Engine::tune_launches(std::string &err, int max_blocks) {
     (void)hipEventDestroy(t1);
     // restore the per-block signal maxima of the current state
     for (const MeshSlot &S : slots_)
-        if (S.used && S.active) CHK(launch_smax(desc_, mp_, U_[0], nullptr, smax_, cmax_, S.first, int(S.plan.n), nvar_, st));
+        if (S.used && S.active) CHK(launch_smax(desc_, mp_, U_[0], nullptr, smax_, cmax_, S.first, int(S.plan.n), nvar_, nullptr, nullptr, st));
     CHK(hipStreamSynchronize(st));
     if (bk[0] == now[0]) bk[0] = kslab;   // the automatic depth stays automatic
     if (bk[1] == now[1]) bk[1] = kslab_last;

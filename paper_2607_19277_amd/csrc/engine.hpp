@@ -37,8 +37,10 @@ hipError_t launch_reflux(const RefluxTask *t, int n, MeshParams *mp, double *U, 
 hipError_t launch_reflux_restrict(const RefluxTask *rt, int nref, const RestrictTask *st, int nres, MeshParams *mp,
                                   double *U, double *XE, const double *freg, double *halo, unsigned long long *smax,
                                   unsigned long long *cmax, int NV, double bw, int last, hipStream_t s);
-hipError_t launch_smax(const BlockDesc *desc, MeshParams *mp, const double *U, double *XE, unsigned long long *smax,
-                       unsigned long long *cmax, int first, int n, int NV, hipStream_t s);
+// src: null, or the caller's state in 16^3 blocks, copied to the pool by map
+hipError_t launch_smax(const BlockDesc *desc, MeshParams *mp, double *U, double *XE, unsigned long long *smax,
+                       unsigned long long *cmax, int first, int n, int NV, const double *src, const int *map,
+                       hipStream_t s);
 hipError_t launch_mesh_reduce(MeshParams *mp, const int *meshes, int nmesh, const unsigned long long *smax,
                               const unsigned long long *cmax, int nmax, int end, hipStream_t s);
 hipError_t launch_mhd_stage(const SweepArgs &a, int stage, int precision, hipStream_t s);
@@ -46,7 +48,7 @@ hipError_t launch_glm_decay(const BlockDesc *desc, MeshParams *mp, double *U, do
                             int nblocks, double hfrac, hipStream_t s);
 hipError_t launch_set_dt(MeshParams *mp, int mesh, double dt, hipStream_t s);
 hipError_t launch_permute(const double *src, double *dst, const int *map, int first, int nblocks, int per_block,
-                          int gather, hipStream_t s);
+                          hipStream_t s);
 hipError_t launch_lohner(const BlockDesc *desc, const double *U, const double *halo, int first, int n, int NV, int v,
                          double eps, double *out, hipStream_t s);
 hipError_t launch_remap(const RemapTask *t, int n, const BlockDesc *desc, const MeshParams *mp, const double *U,

@@ -395,29 +395,38 @@ __global__ __launch_bounds__(256) void k_reflux_restrict(const RefluxTask *__res
     }
 }
 
-// After an upload, pool blocks [first, first + n): per-block maximum signal rate
-// (and, with cmax, the MHD speed max_d |v_d| + c_f,d) and the x-boundary columns
-// of every row into XE, from one read of the state.  A trip is a plane: lane =
-// cell (x, y), and the lanes at x = 0, 1, 14, 15 write the plane's runs of XE.
-// Bound by HBM on large meshes, as the copy of the columns by itself was, whose
-// rows share their cache lines with the rest of the state (512 to 2304 blocks 103 -> 47
-// us on average, 18944 MHD blocks 2747 -> 1430 us).
+// An upload's scan of pool blocks [first, first + n): per-block maximum signal
+// rate (and, with cmax, the MHD speed max_d |v_d| + c_f,d) and the x-boundary
+// columns of every row into XE, from one read of the state.  With src, the state
+// is the caller's (local block q goes to pool block first + map[q]) and is
+// written to the pool on the way.  A trip is two planes: lane = cell (x, y), and
+// the lanes at x = 0, 1, 14, 15 write a plane's runs of XE.  Bound by HBM on
+// large meshes: 512 to 2304 blocks took 55 us for the copy, 58 for the scan and
+// 45 for the columns, whose rows share their cache lines with the rest of the
+// state, each with a read of its own; scan and columns together 47, all 79.
 template <int NV>
-__global__ __launch_bounds__(256) void k_smax(const BlockDesc *desc, MeshParams *mp, const double *__restrict__ U,
+__global__ __launch_bounds__(512) void k_smax(const BlockDesc *desc, MeshParams *mp, double *__restrict__ U,
                                               double *__restrict__ XE, unsigned long long *smax,
-                                              unsigned long long *cmax, int first) {
-    __shared__ unsigned long long sMax[2][4];
-    const int b = first + blockIdx.x;
+                                              unsigned long long *cmax, int first, const double *__restrict__ src,
+                                              const int *map) {
+    __shared__ unsigned long long sMax[2][8];
+    const int b = first + (src ? map[blockIdx.x] : int(blockIdx.x));
     const BlockDesc D = desc[b];
     MeshParams &P = mp[D.mesh];
     const double inv_dx = P.inv_dx1 * double(1 << (D.level - 1));
-    const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
+    const int x = threadIdx.x & 15, y = (threadIdx.x >> 4) & 15;
+    const double *in = src ? src + size_t(blockIdx.x) * NV * CELLS : U + size_t(b) * NV * CELLS;
     unsigned long long m = 0, mc = 0;
     bool ok = true;
-    for (int k = 0; k < BN; ++k) {
+    for (int k = threadIdx.x >> 8; k < BN; k += 2) {
+        const int cell = (k * 16 + y) * 16 + x;
         double u[9];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) u[v] = U[(size_t(b) * NV + v) * CELLS + k * 256 + threadIdx.x];
+        for (int v = 0; v < NV; ++v) u[v] = in[v * CELLS + cell];
+        if (src) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) U[(size_t(b) * NV + v) * CELLS + cell] = u[v];
+        }
         if (XE && ((x + 2) & 15) < 4) {
 #pragma unroll
             for (int v = 0; v < NV; ++v) XE[xe_index(NV, b, k, x >> 3, v) + y * 2 + (x & 1)] = u[v];
@@ -441,7 +450,7 @@ __global__ __launch_bounds__(256) void k_smax(const BlockDesc *desc, MeshParams 
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long r = sMax[0][0], rc = sMax[1][0];
-        for (int w = 1; w < 4; ++w) {
+        for (int w = 1; w < 8; ++w) {
             r = sMax[0][w] > r ? sMax[0][w] : r;
             rc = sMax[1][w] > rc ? sMax[1][w] : rc;
         }
@@ -498,21 +507,20 @@ __global__ void k_set_dt(MeshParams *mp, int mesh, double dt) {
     if (threadIdx.x == 0) mp[mesh].dt = dt;
 }
 
-// Block copies between the caller's order (local index b) and the pool
-// (block first + map[b]); gather = 1: pool -> caller, 0: caller -> pool.  A
-// workgroup copies 1024 words of a block (W: 16 bytes, or 8 when the caller's
-// pointer is only 8-byte aligned), each lane four that are in flight together,
-// streaming.  Bound by HBM on large meshes (4096 blocks 247 -> 230 us, 5.8
-// TB/s) and by latency on small ones, where a workgroup per block left most of
-// the chip idle (64 blocks 33 -> 7.6 us).
+// Block copies from the pool (block first + map[b]) to the caller's order (local
+// index b).  A workgroup copies 1024 words of a block (W: 16 bytes, or 8 when
+// the caller's pointer is only 8-byte aligned), each lane four that are in
+// flight together, streaming.  Bound by HBM on large meshes (4096 blocks 247 ->
+// 230 us, 5.8 TB/s) and by latency on small ones, where a workgroup per block
+// left most of the chip idle (64 blocks 33 -> 7.6 us).
 template <typename W>
 __global__ __launch_bounds__(256) void k_permute(const W *__restrict__ src, W *__restrict__ dst, const int *map,
-                                                 int first, int per_block, int parts, int gather) {
+                                                 int first, int per_block, int parts) {
     const int b = blockIdx.x / parts, part = blockIdx.x - b * parts;
     const size_t o = size_t(first) + map[b];
     const int w = part * 1024 + threadIdx.x;
-    const W *s = src + (gather ? o : size_t(b)) * per_block + w;
-    W *d = dst + (gather ? size_t(b) : o) * per_block + w;
+    const W *s = src + o * per_block + w;
+    W *d = dst + size_t(b) * per_block + w;
     W x[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -635,11 +643,12 @@ hipError_t launch_reflux_restrict(const RefluxTask *rt, int nref, const Restrict
     return hipGetLastError();
 }
 
-hipError_t launch_smax(const BlockDesc *desc, MeshParams *mp, const double *U, double *XE, unsigned long long *smax,
-                       unsigned long long *cmax, int first, int n, int NV, hipStream_t s) {
+hipError_t launch_smax(const BlockDesc *desc, MeshParams *mp, double *U, double *XE, unsigned long long *smax,
+                       unsigned long long *cmax, int first, int n, int NV, const double *src, const int *map,
+                       hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    if (NV == 9) hipLaunchKernelGGL(k_smax<9>, dim3(n), dim3(256), 0, s, desc, mp, U, XE, smax, cmax, first);
-    else hipLaunchKernelGGL(k_smax<5>, dim3(n), dim3(256), 0, s, desc, mp, U, XE, smax, cmax, first);
+    if (NV == 9) hipLaunchKernelGGL(k_smax<9>, dim3(n), dim3(512), 0, s, desc, mp, U, XE, smax, cmax, first, src, map);
+    else hipLaunchKernelGGL(k_smax<5>, dim3(n), dim3(512), 0, s, desc, mp, U, XE, smax, cmax, first, src, map);
     return hipGetLastError();
 }
 
@@ -662,17 +671,17 @@ static bool aligned16(const void *a, const void *b) {
 }
 
 hipError_t launch_permute(const double *src, double *dst, const int *map, int first, int nblocks, int per_block,
-                          int gather, hipStream_t s) {
+                          hipStream_t s) {
     if (nblocks <= 0) return hipSuccess;
     if (per_block % 2 == 0 && aligned16(src, dst)) {
         const int parts = (per_block / 2 + 1023) / 1024;
         hipLaunchKernelGGL(k_permute<double2v>, dim3(unsigned(nblocks) * parts), dim3(256), 0, s,
                            reinterpret_cast<const double2v *>(src), reinterpret_cast<double2v *>(dst), map, first,
-                           per_block / 2, parts, gather);
+                           per_block / 2, parts);
     } else {
         const int parts = (per_block + 1023) / 1024;
         hipLaunchKernelGGL(k_permute<double>, dim3(unsigned(nblocks) * parts), dim3(256), 0, s, src, dst, map, first,
-                           per_block, parts, gather);
+                           per_block, parts);
     }
     return hipGetLastError();
 }
