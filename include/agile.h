@@ -237,13 +237,16 @@ int agile_profile_read(agile_mesh *m, int kind, double *ms_total, int64_t *launc
 
 /* Stage-kernel shape and step options of a mesh.  None of them changes the
  * arithmetic of any cell, so results are bitwise identical for every value.
- *   AGILE_OPT_GRAPH: 1 = agile_step_cfl replays one captured hipGraph per
- *                    step (needs a non-NULL cfg.stream; ignored otherwise and
- *                    while kernel timing is on);
+ *   AGILE_OPT_GRAPH: 1 = agile_step_cfl replays captured hipGraphs: of one
+ *                    step, and after 32 replayed steps of an unchanged mesh of 8
+ *                    steps where a call has as many left (needs a non-NULL
+ *                    cfg.stream; ignored otherwise and while kernel timing is
+ *                    on);
  *   AGILE_OPT_KSLAB: z-planes per workgroup of the stage kernel, 16, 8 or 4
  *                    (smaller slabs give more workgroups for small meshes),
  *                    or 0 (the default): the one that fills the GPU best for
- *                    the number of active blocks; setting it sets
+ *                    the number of active blocks (then 2 or 1 as well on the
+ *                    smallest); setting it sets
  *                    AGILE_OPT_KSLAB_LAST too;
  *   AGILE_OPT_XCD:   1 = each of the 8 XCDs gets one contiguous range of
  *                    blocks (neighbours share that XCD's L2), 0 = the plain

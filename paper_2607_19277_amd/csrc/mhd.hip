@@ -1,8 +1,8 @@
 // mhd.hip -- gfx950 kernels of the ideal-MHD + GLM stage update (Sec. 2.3.3),
 // nvar 9: (rho, m, e, B, psi).
 //
-// A stage is one launch of k_mhd_stage, 256 lanes per block (or per slab of 8
-// or 4 planes on small meshes) marching in z: PLM minmod on primitives, the GLM
+// A stage is one launch of k_mhd_stage, 256 lanes per block (or per slab of 8, 4
+// or 2 planes on small meshes) marching in z: PLM minmod on primitives, the GLM
 // interface step and the HLL flux (mhd_hll) for the z faces from a per-lane
 // register window and for the x and y faces from the plane in LDS, L = -((dFx
 // + dFy) + dFz)/dx, the SSP-RK2 stage combination, flux registers and, in stage
@@ -59,7 +59,7 @@ constexpr int FYTOP = BN * BN, FX = FYTOP + BN, NFX = BN + 1, NFACE = FX + BN * 
 // stages 1 / 2: FP64 5593 / 6515 us with runtime-indexed face tasks and the
 // longer flux, 5041 / 5878 with fixed faces and the shorter flux but 50
 // spilled registers, 4015 / 4910 now (6 and 8 spilled); FP32 flux, 576 blocks:
-// 164 / 226 -> 145 / 178.
+// 164 / 226 -> 139 / 168.
 template <int STAGE, typename R>
 __global__ __launch_bounds__(256, 2) void k_mhd_stage(SweepArgs a) {
     __shared__ R sP[NV][PLANE];

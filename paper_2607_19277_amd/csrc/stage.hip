@@ -86,21 +86,24 @@ __device__ __forceinline__ void to_prim_z(const double C[NV], double gamma, doub
 
 // RS: 0 HLL, 1 HLLC, 2 local Lax-Friedrichs, 3 the SRHD module (local
 // Lax-Friedrichs on (rho, Gamma v, p)); LIM: 0 minmod, 1 van Leer;
-// Bound by VALU issue at 2 waves per SIMD (FP64; 3 with FP32 fluxes): the VALU
-// is busy for 53-65% of a launch, HBM for about half of its time.  Fixed face
-// ownership (no index arithmetic, no rotation selects, own state from
-// registers), ghosts converted once and wave-uniform addresses took an HLLC
-// first stage from 673 to 510 VALU instructions per wave and plane (1856
-// blocks: 263 -> 210 us).  Not faster: three waves per SIMD (168 registers;
-// the face work then spills or loses its instruction-level parallelism, 2-15%
-// slower), the upper faces of 8 planes at once from global memory (balanced
-// over the waves, 4% slower), cells or ghosts loaded one plane further ahead
-// (equal, or up to 3% slower).  On noisy data (256^3 shear layer) the clock drops from 2.39 to
-// 2.04 GHz under this kernel, so there operations cost their energy too.
 // KIND: 1 first stage (U1 = U + dt L), 2 last SSP-RK2 stage
 // ((U^n + (U1 + dt L))/2), 3 middle SSP-RK3 stage (3/4 U^n + 1/4 (U1 + dt L)),
 // 4 last SSP-RK3 stage (1/3 U^n + 2/3 (U2 + dt L)).  The last stage of a step
 // also reduces the signal rate of the new state.
+//
+// Bound by VALU issue at 2 waves per SIMD (FP64; 3 with FP32 fluxes; the VALU
+// is busy for 53-65% of a launch) next to HBM: 1856 blocks, HLLC, FP64 move
+// 0.93 / 1.23 GB (counters) in the first / last stage, 4.5 / 5.4 TB/s against
+// the 6.5 of a copy.  Fixed face ownership (no index arithmetic, no rotation
+// selects, own state from registers), ghosts converted once and wave-uniform
+// addresses took an HLLC first stage from 673 to 510 VALU instructions per wave
+// and plane; with the shorter fluxes, 278 / 308 -> 215 / 241 us (FP32 fluxes
+// 171 / 207).  Not faster: three waves per SIMD (168 registers; the face work
+// then spills or loses its instruction-level parallelism, 2-15% slower), the
+// upper faces of 8 planes at once from global memory (balanced over the waves,
+// 4% slower), cells or ghosts loaded one plane further ahead (equal, or up to
+// 3% slower).  On noisy data (256^3 shear layer) the clock drops from 2.39 to
+// 2.04 GHz under this kernel, so there operations cost their energy too.
 template <int RS, int LIM, int KIND, typename R>
 __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE_STAGE_WAVES_F32) void k_stage(StageArgs a) {
     constexpr bool FIRST = KIND == 1, LAST = KIND == 2 || KIND == 4;
