@@ -127,6 +127,7 @@ struct StageArgs {
     const double *halo;
     double *freg;
     unsigned long long *smax;  // per block: reset in stage 1, maximum in stage 2
+    const unsigned long long *prev;  // first stage of a step in a chain: the maxima of the step before, or null
     const int *list;       // blocks to update (pool indices), or null for [0, nblocks)
     int nblocks;           // number of blocks to update
     int kslab;             // planes per workgroup: 16, 8, 4 or 2 (same arithmetic per cell)
@@ -154,6 +155,11 @@ __device__ __forceinline__ gdouble *uniform_at(const double *base, unsigned off)
 typedef __attribute__((address_space(1))) double2v gdouble2v;
 __device__ __forceinline__ gdouble2v *uniform2_at(const double *base, unsigned off) {
     return (gdouble2v *)uniform_at(base, off);
+}
+// x, the same in every lane, in scalar registers
+__device__ __forceinline__ double uniform(double x) {
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(x)));
 }
 // x, computed anew where it stands: keeps what follows from it (the addresses
 // of rarely taken branches above all) out of registers held across a loop

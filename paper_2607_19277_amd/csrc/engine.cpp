@@ -605,7 +605,7 @@ int Engine::enqueue_correct(int out, double bw, bool last, bool fill, std::strin
 // One stage: kind (1 first, 2 last SSP-RK2, 3 middle / 4 last SSP-RK3) from
 // buffer `in` into buffer `out`, U^n in buffer 0; then the flux correction of
 // the output and, with fill set, the ghost fill of the output.
-int Engine::enqueue_stage(int kind, int in, int out, double bw, bool fill, std::string &err) {
+int Engine::enqueue_stage(int kind, int in, int out, double bw, bool fill, int chain, std::string &err) {
     const hipStream_t st = cfg_.stream;
     const bool last = kind == 2 || kind == 4;
     if (nvar_ == 9) {
@@ -632,7 +632,10 @@ int Engine::enqueue_stage(int kind, int in, int out, double bw, bool fill, std::
     a.mp = mp_;
     a.halo = halo_;
     a.freg = freg_;
-    a.smax = smax_;
+    // the steps of a chain write the two halves of the maxima in turn (Euler and
+    // SRHD leave the second one free)
+    a.smax = smax_ + (chain & 1 ? cfg_.cap_blocks : 0);
+    a.prev = kind == 1 && chain > 0 ? smax_ + (chain & 1 ? 0 : cfg_.cap_blocks) : nullptr;
     a.list = d_list_;
     a.nblocks = nlist_;
     const bool last_kind = kind == 2 || kind == 4;
@@ -649,7 +652,7 @@ int Engine::enqueue_stage(int kind, int in, int out, double bw, bool fill, std::
     return enqueue_correct(out, bw, last, fill, err);
 }
 
-int Engine::enqueue_step(std::string &err) {
+int Engine::enqueue_step(std::string &err, int chain, bool last) {
     const hipStream_t st = cfg_.stream;
     int e;
     const bool mhd = nvar_ == 9;
@@ -660,16 +663,18 @@ int Engine::enqueue_step(std::string &err) {
     if (mhd || !ghosts_valid_)
         if ((e = enqueue_fill(0, err))) return e;
     ghosts_valid_ = false;
-    if ((e = enqueue_stage(1, 0, 1, 1.0, true, err))) return e;
+    if ((e = enqueue_stage(1, 0, 1, 1.0, true, chain, err))) return e;
     if (cfg_.rk == 3) {
-        if ((e = enqueue_stage(3, 1, 2, 0.25, true, err))) return e;
-        if ((e = enqueue_stage(4, 2, 0, 2.0 / 3.0, !mhd, err))) return e;
+        if ((e = enqueue_stage(3, 1, 2, 0.25, true, chain, err))) return e;
+        if ((e = enqueue_stage(4, 2, 0, 2.0 / 3.0, !mhd, chain, err))) return e;
     } else {
-        if ((e = enqueue_stage(2, 1, 0, 0.5, !mhd, err))) return e;
+        if ((e = enqueue_stage(2, 1, 0, 0.5, !mhd, chain, err))) return e;
     }
     // MHD: the second half of the psi decay is applied by the last stage and
     // its flux correction (k_mhd_stage<2>, k_reflux)
-    TIMED(AGILE_K_DT, launch_mesh_reduce(mp_, d_meshes_, nmeshes_, smax_, cmax_, nblocks_max_, 1, st));
+    if (last)
+        TIMED(AGILE_K_DT, launch_mesh_reduce(mp_, d_meshes_, nmeshes_, smax_ + (chain & 1 ? cfg_.cap_blocks : 0), cmax_,
+                                             nblocks_max_, 1, st));
     ghosts_valid_ = !mhd;
     return AGILE_OK;
 }
@@ -687,7 +692,8 @@ int Engine::capture_steps(int steps, StepGraph &G, std::string &err) {
     capturing_ = true;
     std::string e2;
     int rc = AGILE_OK;
-    for (int q = 0; q < steps && !rc; ++q) rc = enqueue_step(e2);
+    const bool ch = chains_steps();
+    for (int q = 0; q < steps && !rc; ++q) rc = enqueue_step(e2, ch ? q : 0, !ch || q == steps - 1);
     capturing_ = false;
     hipGraph_t g = nullptr;
     const hipError_t ec = hipStreamEndCapture(st, &g);
@@ -726,7 +732,8 @@ int Engine::step_cfl(int nsteps, std::string &err) {
             replays_ = std::min(replays_ + done, 4 * GRAPH_STEPS);
             ghosts_valid_ = nvar_ != 9;
         } else {
-            if ((e = enqueue_step(err))) return e;
+            const bool ch = chains_steps();
+            if ((e = enqueue_step(err, ch ? q : 0, !ch || q == nsteps - 1))) return e;
         }
         for (MeshSlot &S : slots_)
             if (S.used && S.active) S.steps_done += done;

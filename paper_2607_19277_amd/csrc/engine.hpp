@@ -223,8 +223,13 @@ private:
     int rebuild(std::string &err);
     int enqueue_fill(int buf, std::string &err, bool restricted = false);
     int enqueue_correct(int out, double bw, bool last, bool fill, std::string &err);
-    int enqueue_stage(int kind, int in, int out, double bw, bool fill, std::string &err);
-    int enqueue_step(std::string &err);
+    int enqueue_stage(int kind, int in, int out, double bw, bool fill, int chain, std::string &err);
+    // chain: steps enqueued since the last reduction; last: reduce after this one
+    int enqueue_step(std::string &err, int chain = 0, bool last = true);
+    // steps follow each other without a reduction between them (k_stage): no
+    // flux correction changes the maxima after the last stage, and a wave holds
+    // those of a mesh.  A profile keeps the reduction's own launches.
+    bool chains_steps() const { return nvar_ != 9 && nreflux_ == 0 && nblocks_max_ <= 64 && !timing_; }
     static constexpr int GRAPH_STEPS = 8;
     struct StepGraph {
         hipGraph_t graph = nullptr;

@@ -49,3 +49,34 @@ def test_graphs_of_several_steps_equal_eager_steps(case):
         same(41)
     g.close()
     e.close()
+
+
+CHAINS = {
+    "one_block": lambda: W.smooth_random(W.uniform_blocks((1, 1, 1)), (1, 1, 1), 1),
+    "full_wave": lambda: W.smooth_random(W.uniform_blocks((4, 4, 4)), (4, 4, 4), 1),
+    "one_more": lambda: W.smooth_random(W.uniform_blocks((13, 5, 1)), (13, 5, 1), 1),
+    "two_level": lambda: W.smooth_random(L2(), (2, 2, 2), 2),
+    "srhd": lambda: W.srhd_smooth_random(W.uniform_blocks((2, 2, 2)), (2, 2, 2), 1),
+}
+
+
+@pytest.mark.parametrize("rk", [2, 3])
+@pytest.mark.parametrize("case", list(CHAINS))
+def test_steps_of_one_call_equal_single_steps(case, rk):
+    import torch
+    from paper_2607_19277_amd import agile as A
+    w = CHAINS[case]()
+    w.rk, w.hi = rk, tuple(float(c) for c in w.base)   # cubic cells
+    a, b = A.Mesh.from_workload(w), A.Mesh.from_workload(w)
+    for n in (1, 2, 5, 4):
+        a.step_cfl(n)
+        for _ in range(n):
+            b.step_cfl(1)
+        torch.cuda.synchronize()
+        assert (a.last_dt(), a.time(), a.dt()) == (b.last_dt(), b.time(), b.dt())
+        assert np.array_equal(a.readback(), b.readback())
+        for m in (a, b):
+            m.step(0.5 * m.dt())
+        assert (a.last_dt(), a.time(), a.dt()) == (b.last_dt(), b.time(), b.dt())
+    a.close()
+    b.close()
