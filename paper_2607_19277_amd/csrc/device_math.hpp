@@ -391,7 +391,8 @@ __device__ __forceinline__ void riemann(const R wL[5], const R wR[5], R gamma, R
 // Newton steps from xi = e kept inside the bracket (bisection otherwise)
 // until a step moves xi by at most 1e-15 xi (at most 100).  IEEE division and
 // square root without contraction: the same iterates as on any machine.  The
-// CFL signal uses this form, so that dt is the same number everywhere.
+// ghost prolongation and the regrid transfer use this form, so that their states
+// are the same bits everywhere.
 __device__ __forceinline__ bool srhd_con2prim(const double U[5], double g, double w[5]) {
 #pragma clang fp contract(off)
     const double D = U[0], e = U[4] + U[0];
@@ -500,14 +501,22 @@ __device__ __forceinline__ bool srhd_con2prim_bracketed(const double U[5], doubl
 }
 
 // The form every cell takes first: Newton alone, without the bracket's
-// selects, in two parts.  Until a step is below 3e-5 xi (the next is then of
-// order 1e-9) reciprocals with one refinement do; the one accurate step that
-// follows leaves an error below rounding, its slope needing no refinement at
-// all.  A lane that leaves (|m|, g e), does not converge in 12 steps or has
-// no state is left to the bracketed form.  The stage kernels of SRHD are bound by
-// this iteration; per cell about 180 issue slots instead of 260 (with the
-// flux below, three SSP-RK3 steps of the 256^3 shear layer 8520 -> 6965 us,
-// with FP32 fluxes 6360 -> 5620 us).
+// selects, in two parts.  Until a step is below 3e-5 xi reciprocals with one
+// refinement do.  The steps that follow are accurate (their slope needs no
+// refinement: its error of 5e-8 counts against the step alone), with the
+// residual as (xi - e) - p, where the first difference is exact.  Newton's
+// constant grows with Gamma^2 (about Gamma^2/6 for cold gas) and an error of xi
+// with 2 Gamma^2 in 1/Gamma^2, so the last step must be below 1e-9 xi / Gamma^2:
+// gas below Gamma of about 2 is done after one accurate step, faster gas takes
+// a second one.  Against the root in extended precision the primitives are
+// 0.85 times as far off as the bracketed form's (median over Gamma 1 to 128,
+// p/rho 1e-4 to 100; nowhere further beyond the noise of rounding).  A lane that leaves (|m|, g e), does not
+// converge (12 and 4 steps; at Gamma above 1000 the arithmetic's noise exceeds the bound)
+// or has no state is left to the bracketed form.  The stage kernels of SRHD are
+// bound by this iteration; per cell about 180 issue slots instead of 260 (with
+// the flux below, three SSP-RK3 steps of the 256^3 shear layer 8520 -> 6965 us,
+// with FP32 fluxes 6360 -> 5620 us; the bound that follows Gamma costs this
+// mild gas nothing, 7021 -> 7006).
 __device__ __forceinline__ bool srhd_con2prim_fast(const double U[5], double g, double w[5]) {
     const double D = U[0], e = U[4] + U[0];
     const double m2 = fma(U[3], U[3], fma(U[2], U[2], U[1] * U[1]));
@@ -527,19 +536,20 @@ __device__ __forceinline__ bool srhd_con2prim_fast(const double U[5], double g, 
         near = __builtin_fabs(dx) <= 3e-5 * x;
         fine = (x * x > m2) & (x < hi);
     }
-    double r = rcp64x2(x);
-    {
+    double r = 0.0;
+    bool conv = false;
+    for (int it = 0; it < 4 && near && !conv; ++it) {
+        r = rcp64x2(x);
         const double q = (m2 * r) * r;
         const double g2 = 1.0 - q;
-        const double G = rsq64x2(g2);
-        const double p = gg * (x * g2 - D * (g2 * G));
-        const double f = (x - p) - e;
-        const double fp = fma(-gg, fma(-((D * G) * q), r, 1.0 + q), 1.0);
+        const double DG = D * rsq64x2(g2);
+        const double f = fma(-(gg * g2), x - DG, x - e);
+        const double fp = fma(-gg, fma(-(DG * q), r, 1.0 + q), 1.0);
         const double dx = f * __builtin_amdgcn_rcp(fp);
         x = x - dx;
-        fine &= near & (__builtin_fabs(dx) <= 1e-6 * x);
-        r = fma(r, fma(-x, r, 1.0), r);
+        conv = __builtin_fabs(dx) <= 1e-9 * (x * g2);
     }
+    r = fma(r, fma(-x, r, 1.0), r);   // x moved by at most 1e-9 of itself
     const double g2 = 1.0 - (m2 * r) * r;
     const double G = rsq64x2(g2);
     const double ig = g2 * G;
@@ -552,7 +562,7 @@ __device__ __forceinline__ bool srhd_con2prim_fast(const double U[5], double g, 
     w[3] = U[3] * rG;
     w[4] = p;
     bool ok = rho > 0.0 && p > 0.0;
-    if (!fine) ok = srhd_con2prim_bracketed(U, g, w);
+    if (!conv) ok = srhd_con2prim_bracketed(U, g, w);
     return ok;
 }
 

@@ -1,0 +1,82 @@
+"""The device's per-cell and per-face arithmetic (csrc/device_math.hpp)
+compiled for the host, against extended precision (64-bit mantissa)."""
+from __future__ import annotations
+
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "host_math")
+LD = np.longdouble
+EPS = 2.0 ** -52
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    assert np.finfo(LD).nmant >= 63
+    so = str(tmp_path_factory.mktemp("host_math") / "host_math.so")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-w", "-ffp-contract=off", "-shared", "-fPIC", f"-I{HERE}",
+                           "-o", so, os.path.join(HERE, "host_math.cpp")])
+    return ctypes.CDLL(so)
+
+
+def _p(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+
+def _srhd_states(rng, n, g, gamma, p_rho):
+    """Conserved SRHD states (D, m, tau) of Lorentz factor `gamma`."""
+    d = rng.normal(size=(n, 3))
+    d *= (np.sqrt(gamma ** 2 - 1.0) / np.linalg.norm(d, axis=1))[:, None]
+    rho = rng.uniform(0.3, 3.0, n)
+    p = p_rho * rho * rng.uniform(0.5, 2.0, n)
+    h = rho + g / (g - 1.0) * p
+    U = np.empty((n, 5))
+    U[:, 0] = gamma * rho
+    U[:, 1:4] = (gamma * h)[:, None] * d
+    U[:, 4] = gamma ** 2 * h - p - U[:, 0]
+    return U
+
+
+def _srhd_prims(U, g):
+    """Primitives by Newton from a bisected bracket, in extended precision."""
+    U = U.astype(LD)
+    g = LD(g)
+    gg = (g - 1) / g
+    D, e = U[:, 0], U[:, 4] + U[:, 0]
+    m2 = (U[:, 1:4] ** 2).sum(axis=1)
+    lo, hi = np.sqrt(m2), g * e
+    x = (lo + hi) / 2
+    for _ in range(150):
+        q = m2 / (x * x)
+        ig = np.sqrt(1 - q)
+        f = x - gg * (x * (1 - q) - D * ig) - e
+        lo, hi = np.where(f > 0, lo, x), np.where(f > 0, x, hi)
+        xn = x - f / (1 - gg * (1 + q - D * q / (ig * x)))
+        x = np.where((xn > lo) & (xn < hi), xn, (lo + hi) / 2)
+    ig = np.sqrt(1 - m2 / (x * x))
+    return np.concatenate([(D * ig)[:, None], U[:, 1:4] / (x * ig)[:, None],
+                           (gg * (x * ig * ig - D * ig))[:, None]], axis=1), x * ig * ig
+
+
+# A root known to a few ulp (the residual's rounding over f' >= 1 - 2 (g-1)/g)
+# moves 1/Gamma^2 = 1 - m^2/xi^2 by 2 Gamma^2 of that, and the pressure, a
+# difference of terms of size rho h, by rho h / p more: 16 ulp times those.
+@pytest.mark.parametrize("g", [4.0 / 3.0, 5.0 / 3.0])
+@pytest.mark.parametrize("gamma", [1.0001, 1.15, 2.0, 5.0, 8.0, 12.0, 16.0, 24.0, 64.0, 100.0, 1000.0])
+def test_srhd_state_recovered_at_every_lorentz_factor(lib, gamma, g):
+    rng = np.random.default_rng(7)
+    for p_rho in (1e-4, 1e-3, 1e-2, 0.1, 1.0, 100.0):
+        U = _srhd_states(rng, 400, g, gamma, p_rho)
+        w = np.empty_like(U)
+        ok = np.empty(len(U), dtype=np.int32)
+        lib.srhd_con2prim(ctypes.c_long(len(U)), _p(U), ctypes.c_double(g), _p(w), _p(ok))
+        R, rhoh = _srhd_prims(U, g)
+        tol = 16 * EPS * gamma ** 2
+        assert ok.all()
+        assert (np.abs(w[:, 0] - R[:, 0]) <= tol * R[:, 0]).all(), p_rho
+        assert (np.abs(w[:, 1:4] - R[:, 1:4]).max(axis=1) <= tol * np.linalg.norm(R[:, 1:4].astype(float), axis=1)).all(), p_rho
+        assert (np.abs(w[:, 4] - R[:, 4]) <= tol * rhoh).all(), p_rho
