@@ -307,7 +307,8 @@ __device__ __forceinline__ double sound_speed64(double rho, double p, double gam
 //   e* = (e_K (S_K - u_K) - p_K u_K + P_K S*)/(S_K - S*).
 // With S_K limited to S_L <= 0 or S_R >= 0 that flux is F_K itself when the
 // flow is supersonic (S_K = 0 leaves rho* S* = rho_K u_K, and so on), so no
-// case is selected after the side.  Davis' speeds give S_L < S* < S_R (the
+// case is selected after the side but S*/(S_K - S*) = -1 at S_K = 0: through the
+// reciprocal of rcp64 the supersonic flux would be off by up to 20 ulp.  Davis' speeds give S_L < S* < S_R (the
 // numerator of S* - S_L is at least gamma (p_L + p_R) - (p_R - p_L) > 0, and
 // likewise on the right), so the sign of S* alone picks the side.
 // The stage kernel is bound by its VALU work and latency, not by HBM, so the
@@ -335,7 +336,7 @@ __device__ __forceinline__ void riemann_euler(const double wL[5], const double w
         const double u = w[1], p = w[4];
         const double du = SK - u;
         const double dK = w[0] * du;
-        const double q = Ss * rcp64(SK - Ss);
+        const double q = SK == 0.0 ? -1.0 : Ss * rcp64(SK - Ss);
         const double PK = fma(dK, Ss - u, p);
         const double vv = fma(w[3], w[3], fma(w[2], w[2], u * u));
         const double e = fma(0.5 * w[0], vv, p * igm1);

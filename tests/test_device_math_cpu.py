@@ -80,3 +80,21 @@ def test_srhd_state_recovered_at_every_lorentz_factor(lib, gamma, g):
         assert (np.abs(w[:, 0] - R[:, 0]) <= tol * R[:, 0]).all(), p_rho
         assert (np.abs(w[:, 1:4] - R[:, 1:4]).max(axis=1) <= tol * np.linalg.norm(R[:, 1:4].astype(float), axis=1)).all(), p_rho
         assert (np.abs(w[:, 4] - R[:, 4]) <= tol * rhoh).all(), p_rho
+
+
+# Supersonic HLLC flux: the physical flux of the upwind side, from products and
+# sums of at most four roundings each of numbers no larger than its terms.
+@pytest.mark.parametrize("mach", [3.0, 10.0, 100.0, 1e4, 1e6])
+@pytest.mark.parametrize("side", [1.0, -1.0])
+def test_supersonic_hllc_flux_is_the_upwind_sides(lib, side, mach):
+    rng = np.random.default_rng(11)
+    g, n = 1.4, 20000
+    c = np.sqrt(g)
+    wL, wR = (np.stack([rng.uniform(0.8, 1.2, n), side * mach * c * rng.uniform(0.8, 1.2, n),
+                        *(mach * c * rng.uniform(-1, 1, (2, n))), rng.uniform(0.8, 1.2, n)], axis=1) for _ in range(2))
+    F = np.empty_like(wL)
+    lib.euler_flux(1, ctypes.c_long(n), _p(wL), _p(wR), ctypes.c_double(g), _p(F))
+    r, u, v, w, p = (wL if side > 0 else wR).astype(LD).T
+    h = p * LD(g) / (LD(g) - 1) + r * (u * u + v * v + w * w) / 2
+    R = np.stack([r * u, r * u * u + p, r * v * u, r * w * u, u * h], axis=1)
+    assert (np.abs(F - R) <= 4 * EPS * np.abs(R)).all(), (np.abs(F - R) / np.abs(R)).max(axis=0)
