@@ -294,13 +294,16 @@ __device__ __forceinline__ double sound_speed64(double rho, double p, double gam
 
 // FP64: the same fluxes with the physical flux written as F = u U + p (0, 1, 0,
 // 0, u), so that neither U nor F of a side is formed.
-// HLL and Lax-Friedrichs are both
-//   F = a U_L + b U_R + (0, al p_L + be p_R, 0, 0, al p_L u_L + be p_R u_R)
-// with, for HLL, al = S_R+/(S_R+ - S_L-), be = -S_L-/(S_R+ - S_L-),
-// a = al (u_L - S_L-), b = be (u_R - S_R+), S+ = max(S, 0), S- = min(S, 0),
-// and for Lax-Friedrichs al = be = 1/2, a = (u_L + s)/2, b = (u_R - s)/2;
-// a and b times the densities give the mass flux of either side, which the
-// velocities then multiply.
+// HLL and Lax-Friedrichs are both al F_L + be F_R + k (U_L - U_R) with, for HLL,
+// al = S_R+/(S_R+ - S_L-), be = -S_L-/(S_R+ - S_L-), k = S_R+ be, S+ = max(S, 0),
+// S- = min(S, 0), and for Lax-Friedrichs al = be = 1/2, k = s/2.  With the mass
+// flux M = al rho_L u_L + be rho_R u_R + k (rho_L - rho_R) and the right
+// side's part B = (be u_R - k) rho_R of it, what the flow carries is M q_L + B
+// (q_R - q_L) for q = u, v_t, v^2/2: differences of the sides before products.
+// (Sums a U_L + b U_R with a = al u_L + k, b = be u_R - k take six
+// operations fewer, LF / van Leer / SSP-RK3 steps on 256^3 4890 instead of 4980
+// us, but in slow flow a rho_L and b rho_R cancel: densities were off by up to
+// 1.5 times as much.)
 // HLLC: across S_K the star state satisfies the jump conditions, so its flux
 // is the physical flux of the state (rho*, S*, v_t, P_K, e*),
 //   rho* = rho_K (S_K - u_K)/(S_K - S*),
@@ -308,14 +311,15 @@ __device__ __forceinline__ double sound_speed64(double rho, double p, double gam
 // With S_K limited to S_L <= 0 or S_R >= 0 that flux is F_K itself when the
 // flow is supersonic (S_K = 0 leaves rho* S* = rho_K u_K, and so on), so no
 // case is selected after the side but S*/(S_K - S*) = -1 at S_K = 0: through the
-// reciprocal of rcp64 the supersonic flux would be off by up to 20 ulp.  Davis' speeds give S_L < S* < S_R (the
-// numerator of S* - S_L is at least gamma (p_L + p_R) - (p_R - p_L) > 0, and
-// likewise on the right), so the sign of S* alone picks the side.
+// reciprocal of rcp64 the supersonic flux would be off by up to 20 ulp (1856-block
+// blast 5180 -> 5205 us).  Davis' speeds give S_L < S* < S_R (the numerator of S* - S_L
+// is at least gamma (p_L + p_R) - (p_R - p_L) > 0, and likewise on the right), so
+// the sign of S* alone picks the side.
 // The stage kernel is bound by its VALU work and latency, not by HBM, so the
 // operation count is what matters: HLLC 71 instructions a face instead of
 // 113.  With the shared minmod bounds above, a pass of ten steps of the
 // 1856-block HLLC blast 6533 -> 6189 us, and of three LF / van Leer / SSP-RK3
-// steps on 256^3 6804 -> 5667 us.
+// steps on 256^3 6804 -> 5667 us (when these fluxes came in).
 template <int RS>
 __device__ __forceinline__ void riemann_euler(const double wL[5], const double wR[5], double gamma, double igm1,
                                               double F[5]) {
@@ -348,30 +352,30 @@ __device__ __forceinline__ void riemann_euler(const double wL[5], const double w
         F[4] = fma(fma(e, du, fma(-p, u, t)), q, t);
         return;
     }
-    double a, b, al, be;
+    double al, be, k;
     if (RS == 2) {
-        const double s = __builtin_fmax(__builtin_fabs(uL) + cL, __builtin_fabs(uR) + cR);
         al = be = 0.5;
-        a = 0.5 * (uL + s);
-        b = 0.5 * (uR - s);
+        k = 0.5 * __builtin_fmax(__builtin_fabs(uL) + cL, __builtin_fabs(uR) + cR);
     } else {
         const double sr = __builtin_fmax(__builtin_fmax(uL + cL, uR + cR), 0.0);
         const double sl = __builtin_fmin(__builtin_fmin(uL - cL, uR - cR), 0.0);
         const double inv = rcp64(sr - sl);
         al = sr * inv;
         be = -sl * inv;
-        a = al * (uL - sl);
-        b = be * (uR - sr);
+        k = sr * be;
     }
-    const double A = a * wL[0], B = b * wR[0];
+    const double a = al * uL, b = be * uR;
+    const double mR = b * wR[0];
+    const double M = fma(k, wL[0] - wR[0], fma(a, wL[0], mR));
+    const double B = fma(-k, wR[0], mR);
     const double vL = fma(wL[3], wL[3], fma(wL[2], wL[2], uL * uL));
     const double vR = fma(wR[3], wR[3], fma(wR[2], wR[2], uR * uR));
-    F[0] = A + B;
-    F[1] = fma(A, uL, B * uR) + (RS == 2 ? 0.5 * (wL[4] + wR[4]) : fma(al, wL[4], be * wR[4]));
-    F[2] = fma(A, wL[2], B * wR[2]);
-    F[3] = fma(A, wL[3], B * wR[3]);
-    const double eL = fma(a, igm1, al * uL), eR = fma(b, igm1, be * uR);
-    F[4] = fma(0.5, fma(A, vL, B * vR), fma(wL[4], eL, wR[4] * eR));
+    F[0] = M;
+    F[1] = fma(M, uL, fma(B, uR - uL, RS == 2 ? 0.5 * (wL[4] + wR[4]) : fma(al, wL[4], be * wR[4])));
+    F[2] = fma(M, wL[2], B * (wR[2] - wL[2]));
+    F[3] = fma(M, wL[3], B * (wR[3] - wL[3]));
+    const double pu = fma(a, wL[4], b * wR[4]);   // e + p = gamma/(gamma - 1) p + rho v^2/2 on either side
+    F[4] = fma(0.5, fma(M, vL, B * (vR - vL)), fma(igm1 * k, wL[4] - wR[4], fma(igm1, pu, pu)));
 }
 
 template <int RS, typename R>

@@ -98,3 +98,26 @@ def test_supersonic_hllc_flux_is_the_upwind_sides(lib, side, mach):
     h = p * LD(g) / (LD(g) - 1) + r * (u * u + v * v + w * w) / 2
     R = np.stack([r * u, r * u * u + p, r * v * u, r * w * u, u * h], axis=1)
     assert (np.abs(F - R) <= 4 * EPS * np.abs(R)).all(), (np.abs(F - R) / np.abs(R)).max(axis=0)
+
+
+# Slow flow of one density and transverse velocity: the mass and transverse
+# momentum fluxes are the weighted mean of two small mass fluxes, each
+# off by the weights' reciprocal (20 ulp) and four roundings of itself; the dissipation
+# (sound speed times density, 1e4 times larger here) has to leave nothing.
+@pytest.mark.parametrize("rs", [0, 2])
+def test_slow_flow_keeps_the_digits_of_its_mass_flux(lib, rs):
+    rng = np.random.default_rng(5)
+    g, n = 1.4, 20000
+    rho, v, w = rng.uniform(0.5, 2.0, n), rng.uniform(-1, 1, n), rng.uniform(-1, 1, n)
+    wL, wR = (np.stack([rho, 1e-4 * rng.uniform(0.5, 1.0, n), v, w, rng.uniform(0.8, 1.2, n)], axis=1) for _ in range(2))
+    F = np.empty_like(wL)
+    lib.euler_flux(rs, ctypes.c_long(n), _p(wL), _p(wR), ctypes.c_double(g), _p(F))
+    L, R = wL.astype(LD), wR.astype(LD)
+    cL, cR = (np.sqrt(LD(g) * q[:, 4] / q[:, 0]) for q in (L, R))
+    sr, sl = np.maximum(L[:, 1] + cL, R[:, 1] + cR), np.minimum(L[:, 1] - cL, R[:, 1] - cR)
+    al = sr / (sr - sl) if rs == 0 else LD(0.5)
+    m = rho * (al * L[:, 1] + (1 - al) * R[:, 1])
+    tol = 24 * EPS * np.abs(m)
+    assert (np.abs(F[:, 0] - m) <= tol).all()
+    assert (np.abs(F[:, 2] - m * v) <= tol * np.abs(v)).all()
+    assert (np.abs(F[:, 3] - m * w) <= tol * np.abs(w)).all()
