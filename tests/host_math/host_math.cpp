@@ -14,3 +14,8 @@ extern "C" void euler_flux(int rs, long n, const double *wL, const double *wR, d
         else agile::riemann<2, double>(wL, wR, gamma, igm1, F);
     }
 }
+
+extern "C" void mhd_flux(long n, const double *wL, const double *wR, double gamma, double ch, double *F) {
+    for (long q = 0; q < n; ++q)
+        agile::mhd_hll(wL + 9 * q, wR + 9 * q, gamma, 1.0 / (gamma - 1.0), ch, 0.5 / ch, F + 9 * q);
+}

@@ -121,3 +121,24 @@ def test_slow_flow_keeps_the_digits_of_its_mass_flux(lib, rs):
     assert (np.abs(F[:, 0] - m) <= tol).all()
     assert (np.abs(F[:, 2] - m * v) <= tol * np.abs(v)).all()
     assert (np.abs(F[:, 3] - m * w) <= tol * np.abs(w)).all()
+
+
+# The same for MHD with a transverse field equal on both sides (its flux is the
+# field times the mean velocity); the weights here carry the fast speeds'
+# error too, up to 17 ulp each.
+def test_slow_mhd_flow_keeps_the_digits_of_its_fluxes(lib):
+    rng = np.random.default_rng(6)
+    g, n = 5.0 / 3.0, 20000
+    rho, v, w, b1, b2 = rng.uniform(0.5, 2.0, n), *rng.uniform(-1, 1, (4, n))
+    zero = np.zeros(n)
+    wL, wR = (np.stack([rho, 1e-4 * rng.uniform(0.5, 1.0, n), v, w, rng.uniform(0.8, 1.2, n), zero, b1, b2, zero],
+                       axis=1) for _ in range(2))
+    F = np.empty_like(wL)
+    lib.mhd_flux(ctypes.c_long(n), _p(wL), _p(wR), ctypes.c_double(g), ctypes.c_double(5.0), _p(F))
+    L, R = wL.astype(LD), wR.astype(LD)
+    cL, cR = (np.sqrt((LD(g) * q[:, 4] + q[:, 6] ** 2 + q[:, 7] ** 2) / q[:, 0]) for q in (L, R))
+    sr, sl = np.maximum(L[:, 1] + cL, R[:, 1] + cR), np.minimum(L[:, 1] - cL, R[:, 1] - cR)
+    al = sr / (sr - sl)
+    u = al * L[:, 1] + (1 - al) * R[:, 1]
+    for var, q in ((0, rho), (2, rho * v), (3, rho * w), (6, b1), (7, b2)):
+        assert (np.abs(F[:, var] - u * q) <= 64 * EPS * np.abs(u * q)).all(), var
