@@ -759,9 +759,12 @@ int Engine::step_dt(int s, double dt, std::string &err) {
 int Engine::fill_ghosts(std::string &err) {
     int e = rebuild(err);
     if (e) return e;
-    if (ghosts_valid_) return AGILE_OK;   // filled by the last step, or since
+    // Euler and SRHD steps leave the ghosts of their result.  MHD steps do not,
+    // and a step that the caller captured is replayed without a call, so what
+    // an earlier MHD fill left is never taken for valid.
+    if (ghosts_valid_) return AGILE_OK;
     if ((e = enqueue_fill(0, err))) return e;
-    ghosts_valid_ = true;
+    ghosts_valid_ = nvar_ != 9;
     return AGILE_OK;
 }
 
@@ -834,8 +837,6 @@ int Engine::remap(int s, const std::vector<RegridSource> &src, double *out_dev, 
             t[i].src[o] = c >= 0 ? S.first + S.plan.perm[c] : -1;
         }
     }
-    int e = fill_ghosts(err);
-    if (e) return e;
     const hipStream_t st = cfg_.stream;
     // XE[1] is free between steps; the mesh's range there, 8 NV KB per block,
     // holds the tasks of the at most 8 new leaves of every block

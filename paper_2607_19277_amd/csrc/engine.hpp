@@ -141,8 +141,10 @@ public:
     // first): per block, in the caller's block order, into host memory.
     int lohner(int slot, int v, double eps, double *out_host, std::string &err);
     // Data of a regridded mesh from this one: src in the caller's block
-    // indices of `slot`, out a device array [src.size()][nvar][16^3].
-    // d_tasks: device room for src.size() task records (null: allocated here).
+    // indices of `slot`, out a device array [src.size()][nvar][16^3].  The
+    // ghosts must be those of the current state (lohner fills them).
+    // d_tasks: device room for src.size() task records (null: the mesh's range
+    // of the x-boundary copy that is free between steps).
     int remap(int slot, const std::vector<RegridSource> &src, double *out_dev, std::string &err,
               RemapTask *d_tasks = nullptr);
     // Whether a mesh with plan P fits once mesh `slot` has been removed.
@@ -261,7 +263,7 @@ private:
     RefluxTask *d_reflux_ = nullptr;
     int nlist_ = 0, nmeshes_ = 0, nblocks_max_ = 0, nrestrict_ = 0, nreflux_ = 0;
     bool rr_indep_ = false;   // flux correction and restriction touch different blocks
-    bool ghosts_valid_ = false;   // halo slabs hold the ghost fill of U[0]
+    bool ghosts_valid_ = false;   // halo slabs hold the ghost fill of U[0] (Euler, SRHD; MHD: never known)
     std::vector<int> pro_off_, pro_cnt_;
     std::vector<char> pro_dep_;   // [level] waits for the level below (some mesh)
     bool dirty_ = true;
