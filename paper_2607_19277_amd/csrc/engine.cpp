@@ -892,8 +892,9 @@ int Engine::read_ghosts(int s, double *out, int out_on_device, std::string &err)
 // a candidate replaces the current shape only when at least 1% faster.
 // Without room for the copy (a caller-owned pool, or the device refuses it)
 // single launches of each stage kind are timed on the current state instead
-// (they only write the stage buffer, its boundary copy, flux registers and
-// the per-block maxima, which are restored or rewritten by the next step);
+// (they only write the stage buffer, its boundary copy, flux registers, the
+// per-block maxima and the non-physical flag, which are restored or rewritten
+// by the next step);
 // that timing does not reproduce a step's cache state, so its choice can
 // differ from the whole-step optimum by a few percent.
 int Engine::tune(std::string &err, int max_blocks) {
@@ -1008,6 +1009,12 @@ int Engine::tune_launches(std::string &err, int max_blocks) {
     const hipStream_t st = cfg_.stream;
     int e;
     if ((e = enqueue_fill(0, err))) return e;
+    // the trials take the dt of the next CFL step and may meet a state that no
+    // step of the program does: the meshes' parameters (their non-physical flag)
+    // are put back afterwards
+    std::vector<MeshParams> keep(size_t(cfg_.cap_meshes));
+    CHK(hipMemcpyAsync(keep.data(), mp_, keep.size() * sizeof(MeshParams), hipMemcpyDeviceToHost, st));
+    CHK(hipStreamSynchronize(st));
     hipEvent_t t0, t1;
     CHK(hipEventCreate(&t0));
     CHK(hipEventCreate(&t1));
@@ -1063,7 +1070,8 @@ int Engine::tune_launches(std::string &err, int max_blocks) {
     }
     (void)hipEventDestroy(t0);
     (void)hipEventDestroy(t1);
-    // restore the per-block signal maxima of the current state
+    // restore the parameters and the per-block signal maxima of the current state
+    CHK(hipMemcpyAsync(mp_, keep.data(), keep.size() * sizeof(MeshParams), hipMemcpyHostToDevice, st));
     for (const MeshSlot &S : slots_)
         if (S.used && S.active) CHK(launch_smax(desc_, mp_, U_[0], nullptr, smax_, cmax_, S.first, int(S.plan.n), nvar_, nullptr, nullptr, st));
     CHK(hipStreamSynchronize(st));
