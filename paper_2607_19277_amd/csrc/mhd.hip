@@ -64,7 +64,7 @@ template <int STAGE, typename R>
 __global__ __launch_bounds__(256, 2) void k_mhd_stage(SweepArgs a) {
     __shared__ R sP[NV][PLANE];
     __shared__ R sF[NV][NFACE];
-    __shared__ double sXE[2 * NV * BN * NG];   // x-boundary columns of a plane's output, as in XE
+    __shared__ __align__(16) double sXE[2 * NV * BN * NG];   // x-boundary columns of a plane's output, as in XE
     const int nslab = BN / a.kslab;
     const int item = blockIdx.x;
     if (item >= a.nblocks * nslab) return;

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 8 ? AGILE_STAGE_WAVES_F64 : AGILE
     __shared__ R sF[2][NV][NFACE];
     // the x-boundary columns of a plane's output, as they stand in XE; stored
     // by consecutive lanes after the next plane's barrier
-    __shared__ double sXE[2][2 * NV * BN * NG];
+    __shared__ __align__(16) double sXE[2][2 * NV * BN * NG];
 
     // work item = (block, slab of kslab planes)
     const int nslab = BN / a.kslab;
