@@ -38,14 +38,11 @@ __device__ __forceinline__ double sqrt64(double x) {
     double d = fma(-g, g, x);
     return x == 0.0 ? 0.0 : fma(d, h, g);
 }
-__device__ __forceinline__ double rcpR(double x) { return rcp64(x); }
+// FP32: the hardware's own
 __device__ __forceinline__ float rcpR(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double sqrtR(double x) { return sqrt64(x); }
+__device__ __forceinline__ float rsqR(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ float sqrtR(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double fminR(double a, double b) { return __builtin_fmin(a, b); }
 __device__ __forceinline__ float fminR(float a, float b) { return __builtin_fminf(a, b); }
-__device__ __forceinline__ double fmaxR(double a, double b) { return __builtin_fmax(a, b); }
-__device__ __forceinline__ double absR(double a) { return __builtin_fabs(a); }
 __device__ __forceinline__ float absR(float a) { return __builtin_fabsf(a); }
 __device__ __forceinline__ float fmaxR(float a, float b) { return __builtin_fmaxf(a, b); }
 
@@ -101,8 +98,6 @@ __device__ __forceinline__ double rsq64(double x) {
     const double e = fma(-x * y, y, 1.0);
     return fma(0.5 * y, e, y);
 }
-__device__ __forceinline__ double rsqR(double x) { return rsq64(x); }
-__device__ __forceinline__ float rsqR(float x) { return __builtin_amdgcn_rsqf(x); }
 
 __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
 #pragma unroll
@@ -190,9 +185,10 @@ __device__ __forceinline__ double signal_rate(const double U[5], double gamma, d
 
 // Conserved state and physical flux of a primitive state rotated to the face
 // normal, (rho, u_n, u_t1, u_t2, p): mass rho u_n, momentum rho u u_n + p e_n,
-// energy u_n (e + p) -- the Euler equations of Sec. 2.3.1.
-template <typename R>
-__device__ __forceinline__ void euler_UF(const R w[5], R igm1, R U[5], R F[5]) {
+// energy u_n (e + p) -- the Euler equations of Sec. 2.3.1.  (FP32; the FP64
+// fluxes form neither.)
+__device__ __forceinline__ void euler_UF(const float w[5], float igm1, float U[5], float F[5]) {
+    using R = float;
     const R rho = w[0], un = w[1], v1 = w[2], v2 = w[3], p = w[4];
     const R vv = (un * un + v1 * v1) + v2 * v2;
     const R e = p * igm1 + R(0.5) * rho * vv;
@@ -202,9 +198,8 @@ __device__ __forceinline__ void euler_UF(const R w[5], R igm1, R U[5], R F[5]) {
 }
 
 // sound speed c = sqrt(gamma p / rho), written as gamma p / sqrt(gamma p rho)
-template <typename R>
-__device__ __forceinline__ R sound_speed(R rho, R p, R gamma) {
-    const R gp = gamma * p;
+__device__ __forceinline__ float sound_speed(float rho, float p, float gamma) {
+    const float gp = gamma * p;
     return gp * rsqR(gp * rho);
 }
 
@@ -580,8 +575,8 @@ __device__ __forceinline__ bool srhd_con2prim_fast(const double U[5], double g, 
 // c_s^2 = g p / (rho h).  With s = 1/sqrt(1 + u^2): Gamma = (1 + u^2) s,
 // v_n = u_n s, v^2 = u^2 s^2, so a state takes one reciprocal square root,
 // two reciprocals and one square root.
-template <typename R>
-__device__ __forceinline__ R srhd_face_state(const R w[5], R ghat, R g, R U[5], R F[5]) {
+__device__ __forceinline__ float srhd_face_state(const float w[5], float ghat, float g, float U[5], float F[5]) {
+    using R = float;
     const R uu = (w[1] * w[1] + w[2] * w[2]) + w[3] * w[3];
     const R G2 = R(1) + uu;
     const R s = rsqR(G2);
