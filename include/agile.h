@@ -136,7 +136,9 @@ int agile_set_blocks(agile_mesh *m, int64_t nblocks, const agile_block_desc *blo
  * from the neighbours and need no fill).  SRHD prolongs the primitives
  * (rho, Gamma v, p) and converts the children back, which keeps them physical
  * next to strong relativistic shocks.  agile_step does this itself; this
- * call exists for inspection.  Errors: AGILE_ESTATE. */
+ * call exists for inspection.  Where the ghosts are known to be those of the
+ * current state (Euler and SRHD: after a step or an earlier fill) nothing is
+ * enqueued.  Errors: AGILE_ESTATE. */
 int agile_fill_ghosts(agile_mesh *m);
 
 /* dt = cfl / max over all leaf cells of sum_d (|v_d| + c_d)/dx_l, for the
@@ -246,12 +248,13 @@ int agile_profile_read(agile_mesh *m, int kind, double *ms_total, int64_t *launc
  *                    (smaller slabs give more workgroups for small meshes),
  *                    or 0 (the default): the one that fills the GPU best for
  *                    the number of active blocks (then 2 or 1 as well on the
- *                    smallest); setting it sets
- *                    AGILE_OPT_KSLAB_LAST too;
+ *                    smallest); setting it sets AGILE_OPT_KSLAB_LAST too.  MHD
+ *                    takes its depth (16, 8, 4 or 2) from the number of
+ *                    active blocks whatever is set here;
  *   AGILE_OPT_XCD:   1 = each of the 8 XCDs gets one contiguous range of
  *                    blocks (neighbours share that XCD's L2), 0 = the plain
- *                    workgroup order (the default); setting it sets
- *                    AGILE_OPT_XCD_LAST too;
+ *                    workgroup order (the default; the only one of MHD);
+ *                    setting it sets AGILE_OPT_XCD_LAST too;
  *   AGILE_OPT_KSLAB_LAST, AGILE_OPT_XCD_LAST: the same for the last stage of
  *                    a step only (the one that also reduces the signal rate);
  *                    the two others then apply to the first and middle stages.
@@ -266,7 +269,8 @@ int agile_mesh_get_option(const agile_mesh *m, int option, int *value);
  * copy of the state, restoring the state after each trial; with a caller-owned
  * pool (or when that copy cannot be allocated) it times single launches of
  * each stage kind reading the current state and writing only the stage
- * buffer.  The mesh state, simulated time and dt are unchanged.  Blocking.
+ * buffer.  The mesh state, simulated time and dt are unchanged.  MHD has
+ * nothing to choose: the call does nothing.  Blocking.
  * Errors: AGILE_ESTATE, AGILE_EDEVICE. */
 int agile_mesh_tune(agile_mesh *m);
 
@@ -429,9 +433,9 @@ int agile_regrid_decide(const agile_config *cfg, int64_t nblocks, const agile_bl
  * staged in the mesh's stage buffer when the new mesh fits in its device
  * memory; otherwise (the mesh grew) a new device pool with room for growth is
  * allocated -- or, with cfg.dev_pool, AGILE_ENOMEM is returned and the mesh
- * is left as it was (this error is not sticky).  A small task table is
- * allocated and freed inside.  stats may
- * be NULL.  Errors: AGILE_EINVAL, AGILE_ESTATE, AGILE_ENOMEM, AGILE_EDEVICE. */
+ * is left as it was (this error is not sticky).  Nothing else is allocated on
+ * the device (the task table takes the place of a copy that is free between
+ * steps).  stats may be NULL.  Errors: AGILE_EINVAL, AGILE_ESTATE, AGILE_ENOMEM, AGILE_EDEVICE. */
 int agile_mesh_regrid(agile_mesh *m, const agile_regrid_params *p, agile_regrid_stats *stats);
 
 /* Regrid without any device allocation, for callers that cannot allocate

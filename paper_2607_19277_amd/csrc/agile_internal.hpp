@@ -130,15 +130,12 @@ struct StageArgs {
     const unsigned long long *prev;  // first stage of a step in a chain: the maxima of the step before, or null
     const int *list;       // blocks to update (pool indices), or null for [0, nblocks)
     int nblocks;           // number of blocks to update
-    int kslab;             // planes per workgroup: 16, 8, 4 or 2 (same arithmetic per cell)
+    int kslab;             // planes per workgroup: 16, 8, 4, 2 or 1 (same arithmetic per cell)
     int xcd;               // 1: XCD-aware workgroup -> block mapping
     int stage;             // stage kind: 1 first, 2 last SSP-RK2, 3 middle / 4 last SSP-RK3
     int limiter;           // 0 minmod, 1 van Leer
 };
 
-// A stage's output and U^n are each touched once per launch: their accesses
-// carry streaming (nontemporal) hints so that they do not displace, in L2, the
-// input planes and ghost rows that neighbouring work items read again.
 // A value at a wave-uniform base plus a lane offset in bytes: base in scalar
 // registers, so that the variables of a cell cost one address
 // computation between them (the compiler would add the variable's stride to

@@ -721,10 +721,15 @@ int Engine::step_cfl(int nsteps, std::string &err) {
                 ghosts_valid_ = true;
             }
             // Launching a graph leaves the GPU idle for about as long as one of
-            // its smallest kernels runs (a step of 8 blocks 24.7 us, in graphs of
-            // 8 steps 21.5; of 64 blocks 38.7 and 35.3).  Meshes that keep stepping get a graph of
-            // several steps; its capture pays off after some tens of steps, so
-            // it is not made for a set of meshes that soon changes.
+            // its smallest kernels runs (8 steps as 8 graphs / one graph: 8 blocks
+            // 197 / 146 us, 64: 309 / 254, 15 on two levels 373 / 337, MHD 668 /
+            // 628, 1856 blocks 4105 / 4065, 512: no difference).  Capturing and
+            // instantiating the graph of 8 steps takes 55 us where they are
+            // chained and 160 to 190 us elsewhere, which those savings repay after
+            // 8 and after 32 to 40 steps; it is made after 32 steps of an
+            // unchanged set of meshes, so that a set that changes earlier does not
+            // pay for it and one that changes just then loses no more than it
+            // would have saved by then.
             if (replays_ >= 4 * GRAPH_STEPS && nsteps - q >= GRAPH_STEPS) done = GRAPH_STEPS;
             StepGraph &G = done == 1 ? graph_one_ : graph_many_;
             if (!G.exec && (e = capture_steps(done, G, err))) return e;
@@ -900,7 +905,7 @@ int Engine::read_ghosts(int s, double *out, int out_on_device, std::string &err)
 int Engine::tune(std::string &err, int max_blocks) {
     int e = rebuild(err);
     if (e) return e;
-    if (nlist_ == 0 || nvar_ == 9) return AGILE_OK;   // the MHD stage has a single shape
+    if (nlist_ == 0 || nvar_ == 9) return AGILE_OK;   // the MHD stage takes its depth from the block count, in the plain order
     const hipStream_t st = cfg_.stream;
     // copy of the state of the active meshes
     const size_t pu = size_t(nvar_) * CELLS, px = size_t(nvar_) * XE_CELLS;

@@ -58,8 +58,9 @@ constexpr int FYTOP = BN * BN, FX = FYTOP + BN, NFX = BN + 1, NFACE = FX + BN * 
 // formed where they are used (opaque), cells converted twice.  18 944 blocks,
 // stages 1 / 2: FP64 5593 / 6515 us with runtime-indexed face tasks and the
 // longer flux, 5041 / 5878 with fixed faces and the shorter flux but 50
-// spilled registers, 4015 / 4910 now (6 and 8 spilled); FP32 flux, 576 blocks:
-// 164 / 226 -> 139 / 168.
+// spilled registers, 4015 / 4910 with 6 and 8 (now 0 and 8; the form of the flux
+// that keeps slow flow's digits takes 3% more VALU instructions, 1.3% of a step);
+// FP32 flux, 576 blocks: 164 / 226 -> 139 / 168.
 template <int STAGE, typename R>
 __global__ __launch_bounds__(256, 2) void k_mhd_stage(SweepArgs a) {
     __shared__ R sP[NV][PLANE];

@@ -91,10 +91,15 @@ __device__ __forceinline__ void to_prim_z(const double C[NV], double gamma, doub
 // 4 last SSP-RK3 stage (1/3 U^n + 2/3 (U2 + dt L)).  The last stage of a step
 // also reduces the signal rate of the new state.
 //
-// Bound by VALU issue at 2 waves per SIMD (FP64; 3 with FP32 fluxes; the VALU
-// is busy for 53-65% of a launch) next to HBM: 1856 blocks, HLLC, FP64 move
-// 0.93 / 1.23 GB (counters) in the first / last stage, 4.5 / 5.4 TB/s against
-// the 6.5 of a copy.  Fixed face ownership (no index arithmetic, no rotation
+// Bound by VALU work and by the waits that 2 waves per SIMD (FP64; 3 with FP32
+// fluxes) do not cover, next to HBM.  Counters of 1856 blocks, HLLC, FP64: of its
+// cycles a wave issues VALU instructions in 35%, waits for memory, LDS or the
+// barrier in 30%, for its turn or a dependency in 22%; with 1.85 waves on a SIMD the
+// VALU is busy for 64% of a launch (256^3 blocks of a shear layer 68%, SRHD 82%).
+// The first / last stage move 0.93 / 1.23 GB, 4.5 / 5.3 TB/s against the 6.5 of a
+// copy.  Output and U^n are each touched once per launch and carry streaming
+// (nontemporal) hints, so that they do not displace, in L2, the input planes and
+// ghost rows that neighbouring work items read again.  Fixed face ownership (no index arithmetic, no rotation
 // selects, own state from registers), ghosts converted once and wave-uniform
 // addresses took an HLLC first stage from 673 to 510 VALU instructions per wave
 // and plane; with the shorter fluxes, 278 / 308 -> 215 / 241 us (FP32 fluxes
