@@ -617,8 +617,13 @@ __device__ __forceinline__ void riemann_srhd(const float wL[5], const float wR[5
 
 // FP64: F = v_n U + p (0, 1, 0, 0, v_n), so that with a = (v_nL + s)/2, b =
 // (v_nR - s)/2 (s the speed) F = a U_L + b U_R + the pressure terms, and
-// neither U nor F of a side is formed; tau = Gamma^2 rho h - p - D leaves
-// s (p_R - p_L)/2 of them in the energy.  The speed is multiplied through by
+// neither U nor F of a side is formed -- but for mass and energy.  The energy
+// flux m_n - D v_n keeps m_n = Gamma rho h u_n (through v_n it would take the
+// error of the estimated Gamma three times), and the dissipation of both is
+// formed from differences, so that it vanishes where the sides agree.  (As a U_L
+// + b U_R throughout, energies after six steps were 1.92e-16 off against 64 bits
+// instead of 1.79e-16; that saves six operations, 6914 instead of 7008 us for the
+// three steps above.)  The speed is multiplied through by
 // h = rho h, with c = g p: (|v_n| (h - c) + sqrt(c X)/Gamma)/(h - v^2 c),
 // X = (h - v^2 c) - v_n^2 (h - c): one reciprocal and two reciprocal square
 // roots a side.
@@ -645,13 +650,15 @@ __device__ __forceinline__ void riemann_srhd(const double wL[5], const double wR
     const double sR = srhd_face_speed(wR, ghat, g, GR, vR, hR);
     const double hs = 0.5 * __builtin_fmax(sL, sR);
     const double a = fma(0.5, vL, hs), b = fma(0.5, vR, -hs);
-    const double A = a * (GL * wL[0]), B = b * (GR * wR[0]);
+    const double DL = GL * wL[0], DR = GR * wR[0];
     const double kL = a * hL, kR = b * hR;
-    F[0] = A + B;
+    const double eL = hL * GL, eR = hR * GR;   // tau + D + p
+    const double tau = (eL - eR) + (wR[4] - wL[4]);   // tau_L - tau_R + D_L - D_R
+    F[0] = fma(hs, DL - DR, 0.5 * fma(vL, DL, vR * DR));
     F[1] = fma(kL, wL[1], kR * wR[1]) + 0.5 * (wL[4] + wR[4]);
     F[2] = fma(kL, wL[2], kR * wR[2]);
     F[3] = fma(kL, wL[3], kR * wR[3]);
-    F[4] = (fma(kL, GL, -A) + fma(kR, GR, -B)) + hs * (wR[4] - wL[4]);
+    F[4] = fma(hs, tau, fma(0.5, fma(hL, wL[1], hR * wR[1]), -F[0]));
 }
 
 // cell signal rate sum_d a_d / dx of a conserved SRHD state: the flux path's

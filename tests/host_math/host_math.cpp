@@ -19,3 +19,8 @@ extern "C" void mhd_flux(long n, const double *wL, const double *wR, double gamm
     for (long q = 0; q < n; ++q)
         agile::mhd_hll(wL + 9 * q, wR + 9 * q, gamma, 1.0 / (gamma - 1.0), ch, 0.5 / ch, F + 9 * q);
 }
+
+extern "C" void srhd_flux(long n, const double *wL, const double *wR, double g, double *F) {
+    for (long q = 0; q < n; ++q)
+        agile::riemann<3, double>(wL + 5 * q, wR + 5 * q, g, 1.0 / (g - 1.0), F + 5 * q);
+}

@@ -142,3 +142,20 @@ def test_slow_mhd_flow_keeps_the_digits_of_its_fluxes(lib):
     u = al * L[:, 1] + (1 - al) * R[:, 1]
     for var, q in ((0, rho), (2, rho * v), (3, rho * w), (6, b1), (7, b2)):
         assert (np.abs(F[:, var] - u * q) <= 64 * EPS * np.abs(u * q)).all(), var
+
+
+# SRHD energy flux of one hot state, m_n - D v_n with m = Gamma rho h u and D v_n
+# = rho u_n: Gamma comes from a reciprocal root within 14 of these eps, once in m
+# and twice in D v_n; six roundings besides.
+def test_srhd_energy_flux_takes_gamma_once(lib):
+    rng = np.random.default_rng(8)
+    g, n = 4.0 / 3.0, 20000
+    u = rng.normal(size=(n, 3))
+    u *= (np.exp(rng.uniform(-1, 3, n)) / np.linalg.norm(u, axis=1))[:, None]
+    rho = rng.uniform(0.5, 2.0, n)
+    w = np.stack([rho, *u.T, 10.0 * rho * rng.uniform(0.5, 2.0, n)], axis=1)
+    F = np.empty_like(w)
+    lib.srhd_flux(ctypes.c_long(n), _p(w), _p(w), ctypes.c_double(g), _p(F))
+    r, u1, u2, u3, p = w.astype(LD).T
+    m = np.sqrt(1 + u1 * u1 + u2 * u2 + u3 * u3) * (r + LD(g) / (LD(g) - 1) * p) * u1
+    assert (np.abs(F[:, 4] - (m - r * u1)) <= EPS * (20 * np.abs(m) + 34 * np.abs(r * u1))).all()
